@@ -548,6 +548,7 @@ struct MarginJob {
   const float* x;
   int64_t n;
   double D;
+  int64_t sig;  // 1 + the field's position among the 1D members of a batch (0: not one)
 };
 
 // ulp(v)^2 = (nextafter(|v|, +Inf) - |v|)^2 from the exponent field e of v:
@@ -608,9 +609,9 @@ __global__ void __launch_bounds__(256) ulp_part_kernel(MarginJob one, const Marg
 // derive mu.  mu_out[field] receives it when given; st (one state per field), when
 // given, receives mu and the bounds that depend on it (E (1 - mu) and the
 // spectral check and projection thresholds), the same values the host fills
-// in when mu is supplied.
+// in when mu is supplied; so does the descriptor in sigs of a 1D member of a batch.
 __global__ void __launch_bounds__(256) margin_kernel(const double* part, MarginJob one, const MarginJob* jobs, int dt,
-                                                     double* mu_out, DevState* st) {
+                                                     double* mu_out, DevState* st, SigDesc* sigs = nullptr) {
   __shared__ double red[4];
   const MarginJob jb = jobs ? jobs[blockIdx.x] : one;
   const int nslot = ulp_slots(jb.n);
@@ -631,6 +632,14 @@ __global__ void __launch_bounds__(256) margin_kernel(const double* part, MarginJ
     spectral_thresholds(dt, t->Delta, mu, &dc, &dp);
     t->Dc = dc;
     t->Dp = dp;
+  }
+  if (sigs && jb.sig > 0) {  // a 1D member of a batch: its descriptor's thresholds
+    SigDesc* d = sigs + (jb.sig - 1);
+    d->Ep = d->E * (1.0 - mu);
+    double dc, dp;
+    spectral_thresholds(dt, d->Delta, mu, &dc, &dp);
+    d->Dc = dc;
+    d->Dp = dp;
   }
 }
 
@@ -1178,20 +1187,23 @@ thread_local HostBuf g_host_sig, g_host_sigstate;
 struct Streams {
   // cap, cap2: capture (the second for a graph's parallel branch); side: the 1D members of a
   // mixed batch; side2: the 1D members that run one block each
-  hipStream_t cap = nullptr, cap2 = nullptr, side = nullptr, side2 = nullptr;
+  // lane1, lane2 (cap3 under capture): 1D length classes beside those on the class lane 0
+  hipStream_t cap = nullptr, cap2 = nullptr, cap3 = nullptr, side = nullptr, side2 = nullptr, lane1 = nullptr,
+              lane2 = nullptr;
   hipEvent_t fork = nullptr, join = nullptr, fork2 = nullptr, join2 = nullptr, ready1d = nullptr, looped = nullptr,
-             cfork = nullptr, cjoin = nullptr;
+             cfork = nullptr, cjoin = nullptr, lfork = nullptr, ljoin[2] = {nullptr, nullptr};
   ~Streams() {
-    for (hipStream_t q : {cap, cap2, side, side2})
+    for (hipStream_t q : {cap, cap2, cap3, side, side2, lane1, lane2})
       if (q) (void)hipStreamDestroy(q);
-    for (hipEvent_t ev : {fork, join, fork2, join2, ready1d, looped, cfork, cjoin})
+    for (hipEvent_t ev : {fork, join, fork2, join2, ready1d, looped, cfork, cjoin, lfork, ljoin[0], ljoin[1]})
       if (ev) (void)hipEventDestroy(ev);
   }
   hipError_t ready() {
     hipError_t e = hipSuccess;
-    for (hipStream_t* q : {&cap, &cap2, &side, &side2})
+    for (hipStream_t* q : {&cap, &cap2, &cap3, &side, &side2, &lane1, &lane2})
       if (e == hipSuccess && !*q) e = hipStreamCreateWithFlags(q, hipStreamNonBlocking);
-    for (hipEvent_t* ev : {&fork, &join, &fork2, &join2, &ready1d, &looped, &cfork, &cjoin})
+    for (hipEvent_t* ev : {&fork, &join, &fork2, &join2, &ready1d, &looped, &cfork, &cjoin, &lfork, &ljoin[0],
+                           &ljoin[1]})
       if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
     return e;
   }
@@ -1691,7 +1703,7 @@ struct GroupRun {
       double* slots = (double*)(ws + p.off_ulp);
       const double mu_given = mus ? mus[0] : 0.0;
       if (p.dt == FFCZ_F32 && !(mu_given > 0.0)) {
-        const MarginJob one_job{(const float*)inst[0].x_orig, p.N, 0.0};
+        const MarginJob one_job{(const float*)inst[0].x_orig, p.N, 0.0, 0};
         hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)ulp_slots(p.N)), dim3(256), 0, s, one_job,
                            (const MarginJob*)nullptr, slots);
         HIPCHK(hipGetLastError());
@@ -1710,7 +1722,7 @@ struct GroupRun {
       const int nsl = ulp_slots(p.N);
       double* slots = (double*)(ws + p.off_ulp);
       if (p.dt == FFCZ_F32) {
-        const MarginJob one_job{(const float*)inst[0].x_orig, p.N, inst[0].delta_f};
+        const MarginJob one_job{(const float*)inst[0].x_orig, p.N, inst[0].delta_f, 0};
         hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)nsl), dim3(256), 0, s, one_job, (const MarginJob*)nullptr,
                            slots);
         HIPCHK(hipGetLastError());
@@ -1728,7 +1740,7 @@ struct GroupRun {
       if (p.B != 1 || p.dt != FFCZ_F32) return fail(FFCZ_E_INVALID, "device margin needs one FP32 instance");
       const int nsl = ulp_slots(p.N);
       double* slots = (double*)(ws + p.off_ulp);
-      const MarginJob one_job{(const float*)inst[0].x_orig, p.N, inst[0].delta_f};
+      const MarginJob one_job{(const float*)inst[0].x_orig, p.N, inst[0].delta_f, 0};
       hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)nsl), dim3(256), 0, s, one_job, (const MarginJob*)nullptr,
                          slots);
       HIPCHK(hipGetLastError());
@@ -2020,49 +2032,85 @@ McTabs mc_tabs(int dt, int lgMc) {
   return t;
 }
 
-// W_Mc^{n1 k2} in the column layout [k2][n1] and in the row-pass layout of the sig kernel
-__global__ void tw4_kernel(void* col, void* row, int dbl, int lgMc, int MA, int RR) {
-  const int64_t Mc = (int64_t)1 << lgMc;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Mc) return;
-  const int64_t k2 = i / MA, n1 = i % MA;
-  const int64_t r = (n1 * k2) & (Mc - 1);
-  double sn, cs;
-  sincospi(-2.0 * (double)r / (double)Mc, &sn, &cs);
-  const int64_t rp = ((k2 / RR) * MA + n1) * RR + (k2 % RR);
-  if (dbl) {
-    ((cx<double>*)col)[i] = cx<double>{cs, sn};
-    ((cx<double>*)row)[rp] = cx<double>{cs, sn};
-  } else {
-    ((cx<float>*)col)[i] = cx<float>{__double2float_rn(cs), __double2float_rn(sn)};
-    ((cx<float>*)row)[rp] = cx<float>{__double2float_rn(cs), __double2float_rn(sn)};
-  }
-}
+// The four-step tables of every length class of a call, in one launch (bound by its own start:
+// 2^20 entries of all classes take about 10 us, where a launch per table and precision, 4 per
+// class, took about 10 us each).  Blocks [first, next class's first) serve a class: entry i < Mc
+// is W_Mc^{n1 k2} in the column layout [k2][n1] and in the row-pass layout of the sig kernel,
+// the rest are the stage twiddles of its two transform lengths.  Each value is computed once in
+// FP64 and stored in FP64 and in the working type.  The grid's last blocks clear the 1D
+// members' loop states.
+struct TabClass {
+  char* base;
+  McTabs t;
+  int32_t lgMc, MA, RR;
+  int32_t first;  // first block
+};
+struct TabClasses {
+  TabClass c[20];
+  int32_t n, dbl;
+  unsigned long long* zero;
+  int64_t nzero;
+  int32_t zfirst;  // first clearing block
+};
 
-hipError_t write_mc_tabs(int dt, int lgMc, char* base, const McTabs& t, hipStream_t s) {
-  const int MA = sig_ma(lgMc), MB = (1 << lgMc) / MA;
-  const int64_t Mc = (int64_t)1 << lgMc;
-  for (int pass = 0; pass < 2; ++pass) {
-    const int dbl = (pass == 1 || dt == FFCZ_F64) ? 1 : 0;
-    char* col = base + (pass ? t.tw4_64 : t.tw4);
-    char* row = base + (pass ? t.tw4r_64 : t.tw4r);
-    hipLaunchKernelGGL(tw4_kernel, dim3((unsigned)((Mc + 255) / 256)), dim3(256), 0, s, col, row, dbl, lgMc, MA,
-                       sig_rows_per_tile(dbl, lgMc));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    TwJobs ja, jb;
-    memset(&ja, 0, sizeof(ja));
-    ja.dbl = dbl;
-    ja.n = 1;
-    jb = ja;
-    ja.j[0] = TwJob{0, MA, pick_E(MA), 0};
-    jb.j[0] = TwJob{0, MB, pick_E(MB), 0};
-    hipLaunchKernelGGL(twiddle_kernel, dim3(64, 2), dim3(256), 0, s, (void*)(base + (pass ? t.twa_64 : t.twa)), ja,
-                       (void*)(base + (pass ? t.twb_64 : t.twb)), jb);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+__global__ void __launch_bounds__(256) sig_tables_kernel(TabClasses J) {
+  if ((int)blockIdx.x >= J.zfirst) {
+    const int64_t i = (int64_t)((int)blockIdx.x - J.zfirst) * 256 + threadIdx.x;
+    if (i < J.nzero) J.zero[i] = 0ull;
+    return;
   }
-  return hipSuccess;
+  int k = 0;
+  while (k + 1 < J.n && (int)blockIdx.x >= J.c[k + 1].first) ++k;
+  const TabClass& c = J.c[k];
+  const int64_t Mc = (int64_t)1 << c.lgMc, i = (int64_t)((int)blockIdx.x - c.first) * 256 + threadIdx.x;
+  const int MA = c.MA, MB = (int)(Mc / MA);
+  double sn, cs;
+  size_t o0, o1, o0_64, o1_64;  // byte offsets of the tables an entry goes to
+  int64_t e0, e1;               // and its indices there
+  if (i < Mc) {
+    const int64_t k2 = i / MA, n1 = i % MA;
+    const int64_t r = (n1 * k2) & (Mc - 1);
+    sincospi(-2.0 * (double)r / (double)Mc, &sn, &cs);
+    e0 = i;
+    e1 = ((k2 / c.RR) * MA + n1) * c.RR + (k2 % c.RR);
+    o0 = c.t.tw4;
+    o1 = c.t.tw4r;
+    o0_64 = c.t.tw4_64;
+    o1_64 = c.t.tw4r_64;
+  } else {
+    // stage twiddle e of length L: stage of span ns owns ns (E - 1) entries (host_twsize)
+    const int ta = host_twsize(MA, pick_E(MA)), tb = host_twsize(MB, pick_E(MB));
+    int64_t e = i - Mc;
+    const bool second = e >= ta;
+    if (second) e -= ta;
+    if (second && e >= tb) return;
+    const int L = second ? MB : MA, E = pick_E(L);
+    const int lgE = ilog2c(E), a = ilog2c(L) / lgE;
+    const int r0 = L >> (a * lgE);
+    int64_t ns = r0 > 1 ? r0 : 1, off = 0;
+    for (int t = 0; t < a; ++t, ns *= E) {
+      if (ns == 1) continue;
+      const int64_t own = ns * (E - 1);
+      if (e < off + own) break;
+      off += own;
+    }
+    const int64_t loc = e - off, m = loc / (E - 1), r = loc % (E - 1) + 1;
+    sincospi(-2.0 * (double)(m * r) / ((double)ns * E), &sn, &cs);
+    e0 = e1 = e;
+    o0 = o1 = second ? c.t.twb : c.t.twa;
+    o0_64 = o1_64 = second ? c.t.twb_64 : c.t.twa_64;
+  }
+  const cx<double> w{cs, sn};
+  ((cx<double>*)(c.base + o0_64))[e0] = w;
+  ((cx<double>*)(c.base + o1_64))[e1] = w;
+  if (J.dbl) {
+    ((cx<double>*)(c.base + o0))[e0] = w;
+    ((cx<double>*)(c.base + o1))[e1] = w;
+  } else {
+    const cx<float> f{__double2float_rn(cs), __double2float_rn(sn)};
+    ((cx<float>*)(c.base + o0))[e0] = f;
+    ((cx<float>*)(c.base + o1))[e1] = f;
+  }
 }
 
 // Layout of the batched workspace
@@ -2151,14 +2199,15 @@ int32_t batch_plan(int32_t dt, int32_t count, const ffcz_instance* inst, int32_t
     bp.tpart_tiles[kv.first] = pt;
     off = align_up(off + sizeof(unsigned long long) * SP_KINDS * kv.second.size() * (size_t)pt, 256);
   }
+  // margin jobs (x pointer, length, bound), descriptors and block order: one upload
+  bp.off_mjobs = off;
+  off = align_up(off + sizeof(MarginJob) * (size_t)std::max(count, 1), 256);
   bp.off_desc = off;
   off = align_up(off + sizeof(SigDesc) * (size_t)std::max(ns, 1), 256);
-  bp.off_sstats = off;
-  off = align_up(off + sizeof(SigStats) * (size_t)std::max(ns, 1), 256);
   bp.off_order = off;
   off = align_up(off + sizeof(int32_t) * (size_t)std::max(ns, 1), 256);
-  bp.off_mjobs = off;  // margin jobs (x pointer, length, bound)
-  off = align_up(off + sizeof(MarginJob) * (size_t)std::max(count, 1), 256);
+  bp.off_sstats = off;
+  off = align_up(off + sizeof(SigStats) * (size_t)std::max(ns, 1), 256);
   bp.off_msum = off;  // margin partial sums (kUlpSlots per member), then the members' mu
   off = align_up(off + sizeof(double) * (size_t)(kUlpSlots + 1) * (size_t)std::max(count, 1), 256);
   bp.bytes = off;
@@ -2299,19 +2348,30 @@ hipError_t sig_launch(int dt, int mode, int lgMc, const BatchPlan& bp, char* ws,
   return launch_sig(dt, mode, lgMc, &a, nsig, s);
 }
 
-// Descriptors (bounds, thresholds, buffer addresses) and block order of the 1D members, and
-// the four-step tables of every length class; first[lg] is the class's first slot in the order.
-int32_t sig_prepare(const BatchPlan& bp, const ffcz_instance* inst, const double* mus, char* ws, hipStream_t s,
-                    HostBuf& hsig, std::map<int, int>& first) {
+// Margin jobs of every member, and descriptors (bounds, thresholds, buffer addresses) and block
+// order of the 1D members, uploaded together; first[lg] is a class's first slot in the order.
+// Without mus the descriptors' thresholds are left to margin_kernel.
+int32_t sig_stage(const BatchPlan& bp, int32_t count, const ffcz_instance* inst, const double* mus, char* ws,
+                  hipStream_t s, HostBuf& hsig, std::map<int, int>& first) {
   const int ns = (int)bp.sig_ids.size();
-  // own staging buffer: the grouped members reuse g_host_init while these copies may be in flight
-  HIPCHK(hsig.reserve(sizeof(SigDesc) * ns + sizeof(int32_t) * ns));
-  SigDesc* hd = (SigDesc*)hsig.p;
-  int32_t* ho = (int32_t*)(hd + ns);
+  // own staging buffer: the grouped members reuse g_host_init while this copy may be in flight
+  const size_t bytes = bp.off_order + sizeof(int32_t) * (size_t)ns - bp.off_mjobs;
+  HIPCHK(hsig.reserve(bytes));
+  char* const h = (char*)hsig.p;
+  MarginJob* hj = (MarginJob*)h;
+  SigDesc* hd = (SigDesc*)(h + (bp.off_desc - bp.off_mjobs));
+  int32_t* ho = (int32_t*)(h + (bp.off_order - bp.off_mjobs));
+  for (int i = 0; i < count; ++i) {
+    int64_t N = 1;
+    for (int d = 0; d < inst[i].ndim; ++d) N *= inst[i].shape[d];
+    hj[i] = MarginJob{(const float*)inst[i].x_orig, N, inst[i].delta_f, 0};
+  }
   for (int k = 0; k < ns; ++k) {
-    const ffcz_instance& in = inst[bp.sig_ids[k]];
+    const int id = bp.sig_ids[k];
+    const ffcz_instance& in = inst[id];
     const SigPlan& sp = bp.sigs[k];
     char* b = ws + bp.sig_off[k];
+    hj[id].sig = k + 1;
     SigDesc d;
     memset(&d, 0, sizeof(d));
     d.x = in.x_orig;
@@ -2321,8 +2381,10 @@ int32_t sig_prepare(const BatchPlan& bp, const ffcz_instance* inst, const double
     d.blue = sp.blue;
     d.E = in.eps_s;
     d.Delta = in.delta_f;
-    d.Ep = in.eps_s * (1.0 - mus[bp.sig_ids[k]]);
-    spectral_thresholds(bp.dt, in.delta_f, mus[bp.sig_ids[k]], &d.Dc, &d.Dp);
+    if (mus) {
+      d.Ep = in.eps_s * (1.0 - mus[id]);
+      spectral_thresholds(bp.dt, in.delta_f, mus[id], &d.Dc, &d.Dp);
+    }
     d.conv = b + sp.conv64;
     d.conv64 = b + sp.conv64;
     if (sp.blue) {
@@ -2344,10 +2406,36 @@ int32_t sig_prepare(const BatchPlan& bp, const ffcz_instance* inst, const double
     first[kv.first] = pos;
     for (int id : ids) ho[pos++] = id;
   }
-  HIPCHK(hipMemcpyAsync(ws + bp.off_desc, hd, sizeof(SigDesc) * ns, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(ws + bp.off_order, ho, sizeof(int32_t) * ns, hipMemcpyHostToDevice, s));
-  for (auto& kv : bp.by_mc)
-    HIPCHK(write_mc_tabs(bp.dt, kv.first, ws + bp.mc_off.at(kv.first), bp.mc_tab.at(kv.first), s));
+  HIPCHK(hipMemcpyAsync(ws + bp.off_mjobs, h, bytes, hipMemcpyHostToDevice, s));
+  return FFCZ_OK;
+}
+
+// The four-step tables of every length class, and cleared loop states (one launch).
+int32_t sig_tables(const BatchPlan& bp, char* ws, hipStream_t s) {
+  if (bp.sig_ids.empty()) return FFCZ_OK;
+  TabClasses J;
+  memset(&J, 0, sizeof(J));
+  int32_t nb = 0;
+  for (auto& kv : bp.by_mc) {
+    const int lg = kv.first, MA = sig_ma(lg), MB = (1 << lg) / MA;
+    if (J.n >= 20) return fail(FFCZ_E_SHAPE, "too many 1D length classes");
+    TabClass& c = J.c[J.n++];
+    c.base = ws + bp.mc_off.at(lg);
+    c.t = bp.mc_tab.at(lg);
+    c.lgMc = lg;
+    c.MA = MA;
+    c.RR = sig_rows_per_tile(0, lg);
+    c.first = nb;
+    const int64_t n = ((int64_t)1 << lg) + host_twsize(MA, pick_E(MA)) + host_twsize(MB, pick_E(MB));
+    nb += (int32_t)((n + 255) / 256);
+  }
+  J.dbl = bp.dt == FFCZ_F64 ? 1 : 0;
+  J.zero = (unsigned long long*)(ws + bp.off_sstats);
+  J.nzero = (int64_t)(bp.sig_ids.size() * sizeof(SigStats) / 8);
+  J.zfirst = nb;
+  nb += (int32_t)((J.nzero + 255) / 256);
+  hipLaunchKernelGGL(sig_tables_kernel, dim3((unsigned)nb), dim3(256), 0, s, J);
+  HIPCHK(hipGetLastError());
   return FFCZ_OK;
 }
 
@@ -2431,49 +2519,60 @@ hipError_t sig_trial(const BatchPlan& bp, char* ws, const int32_t* ord, int lg, 
 }
 
 // Time both forms of every class the tuner decides and has no entry for, on the call's own
-// members (three fixed rounds each, before the real run; nothing else runs meanwhile).
-int32_t pretune_sigs(const BatchPlan& bp, const ffcz_instance* inst, const double* mus, const ffcz_options& o,
-                     char* ws, hipStream_t s, HostBuf& hsig) {
+// members (staged, with tables; three fixed rounds each, before the real run; nothing else runs
+// meanwhile).
+int32_t pretune_sigs(const BatchPlan& bp, const ffcz_options& o, char* ws, hipStream_t s,
+                     const std::map<int, int>& first) {
   if (bp.sig_ids.empty() || o.tiled_1d_lg > 0) return FFCZ_OK;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIPCHK(hipStreamIsCapturing(s, &cs));
   if (cs != hipStreamCaptureStatusNone) return FFCZ_OK;  // nothing is timed under capture
-  std::map<int, int> first;
-  bool prepared = false;
+  bool ran = false;
   for (auto& kv : bp.by_mc) {
     const int lg = kv.first;
     if (lg < kSigTiledMinLg || lg > kSigTuneMaxLg) continue;
-    if (!prepared) {
-      int32_t r = sig_prepare(bp, inst, mus, ws, s, hsig, first);
-      if (r != FFCZ_OK) return r;
-      prepared = true;
-    }
-    const int32_t* ord = (const int32_t*)(ws + bp.off_order) + first[lg];
+    const int32_t* ord = (const int32_t*)(ws + bp.off_order) + first.at(lg);
     const bool dflt = sig_default_tiled(lg);
     int v = 0;
     int32_t r = tune_pass(sig_tune_key(bp, lg), s, true, 0.9f, 2, [&](int var) {
       const bool tiled = dflt != (var == 1);
+      ran = true;
       return bp.dt == FFCZ_F32 ? sig_trial<float>(bp, ws, ord, lg, tiled, o.resident_1d != 0, 3, s)
                                : sig_trial<double>(bp, ws, ord, lg, tiled, o.resident_1d != 0, 3, s);
     }, &v);
     if (r != FFCZ_OK) return r;
   }
+  if (ran) {  // the trials used the loop states
+    const int64_t n = (int64_t)(bp.sig_ids.size() * sizeof(SigStats) / 8);
+    hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                       (unsigned long long*)(ws + bp.off_sstats), n);
+    HIPCHK(hipGetLastError());
+  }
   return FFCZ_OK;
 }
 
-// The 1D members of a batch in phases: begin (descriptors and tables, the one-block classes on
-// their own stream, the tiled classes' set-up), the tiled rounds in chunks (run here, or
-// captured with the groups' rounds by the mixed-batch loop), end (the tiled classes' outputs and
-// verification, then the one-block stream joined).  Every tiled round pass returns at entry once
-// its signal's loop has ended.
+// Streams that independent length classes run on side by side: lane 0 is the stream that the
+// work belongs to, the others are forked from it and joined into it.
+struct SigLanes {
+  int n = 1;
+  hipStream_t q[3] = {nullptr, nullptr, nullptr};
+};
+
+// The 1D members of a batch in phases: begin (descriptors and tables are in place; the one-block
+// classes on their own stream, the tiled classes' set-up), the tiled rounds in chunks (run here,
+// or captured with the groups' rounds by the mixed-batch loop), end (the tiled classes' outputs
+// and verification, then the one-block stream joined).  Every tiled round pass returns at entry
+// once its signal's loop has ended.  A pass of one class is a small launch (10 to 40 us, mostly
+// ramp and tail, few blocks for the shorter classes) and classes do not depend on each other, so
+// they run in lanes: 128 EEG-like signals of 2^12 to 2^18 samples, one round of their five
+// tiled classes one after another 450 us.
 struct SigRun {
   const BatchPlan* bp = nullptr;
-  const ffcz_instance* inst = nullptr;
-  const double* mus = nullptr;
   int32_t max_iter = 0;
   ffcz_options o{};
   char* ws = nullptr;
-  hipStream_t s = nullptr;       // set-up, tiled passes, end
+  hipStream_t s = nullptr;       // set-up, tiled passes, end (lane 0)
+  SigLanes lanes;                // the streams of set-up and end
   hipStream_t side = nullptr;    // one-block classes (joined into s at the end)
   hipEvent_t fork = nullptr, join = nullptr;
   std::map<int, int> first;      // class -> first slot in the block order
@@ -2493,28 +2592,62 @@ struct SigRun {
     return sig_launch<float>(bp->dt, mode, lg, *bp, ws, ord, nb, max_iter, fixed, st);
   }
 
-  int32_t begin(const BatchPlan& bp_, const ffcz_instance* inst_, const double* mus_, int32_t max_iter_,
-                const ffcz_options& o_, char* ws_, hipStream_t s_, hipStream_t side_, hipEvent_t fork_,
-                hipEvent_t join_, HostBuf& hsig) {
+  int lanes_used(const SigLanes& L) const { return std::min<int>(L.n, (int)tiled.size()); }
+
+  // f(class, stream) for every tiled class, classes spread over the lanes by their work (entries
+  // of all signals; largest first onto the least loaded lane)
+  template <typename F>
+  hipError_t spread(const SigLanes& L, F&& f) const {
+    const int n = lanes_used(L);
+    std::vector<std::pair<int64_t, int>> w;
+    for (int lg : tiled) w.push_back({(int64_t)bp->by_mc.at(lg).size() << lg, lg});
+    std::sort(w.rbegin(), w.rend());
+    hipError_t e = hipSuccess;
+    int64_t load[3] = {0, 0, 0};
+    for (size_t i = 0; i < w.size() && e == hipSuccess; ++i) {
+      int k = 0;
+      for (int j = 1; j < n; ++j)
+        if (load[j] < load[k]) k = j;
+      load[k] += w[i].first;
+      e = f(w[i].second, L.q[k]);
+    }
+    return e;
+  }
+
+  // spread, with the other lanes forked from lane 0 before and joined into it after (also when a
+  // launch failed)
+  template <typename F>
+  hipError_t across(const SigLanes& L, F&& f) const {
+    const int n = lanes_used(L);
+    hipError_t e = hipSuccess;
+    if (n > 1) e = hipEventRecord(g_streams.lfork, L.q[0]);
+    for (int k = 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(L.q[k], g_streams.lfork, 0);
+    if (e != hipSuccess) return e;
+    e = spread(L, f);
+    for (int k = 1; k < n; ++k) {
+      hipError_t j = hipEventRecord(g_streams.ljoin[k - 1], L.q[k]);
+      if (j == hipSuccess) j = hipStreamWaitEvent(L.q[0], g_streams.ljoin[k - 1], 0);
+      if (e == hipSuccess) e = j;
+    }
+    return e;
+  }
+
+  int32_t begin(const BatchPlan& bp_, int32_t max_iter_, const ffcz_options& o_, char* ws_,
+                const std::map<int, int>& first_, const SigLanes& lanes_, hipStream_t side_, hipEvent_t fork_,
+                hipEvent_t join_) {
     bp = &bp_;
-    inst = inst_;
-    mus = mus_;
     max_iter = max_iter_;
     o = o_;
     ws = ws_;
-    s = s_;
+    first = first_;
+    lanes = lanes_;
+    s = lanes.q[0];
     side = side_;
     fork = fork_;
     join = join_;
     fixed = o.fixed_iterations ? 1 : 0;
     chunk = o.graph_chunk > 0 ? o.graph_chunk : 4;
-    const int ns = nsig();
-    if (ns == 0) return FFCZ_OK;
-    int32_t pr = sig_prepare(*bp, inst, mus, ws, s, hsig, first);
-    if (pr != FFCZ_OK) return pr;
-    hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((ns * sizeof(SigStats) / 8 + 255) / 256)), dim3(256), 0, s,
-                       (unsigned long long*)(ws + bp->off_sstats), (int64_t)(ns * sizeof(SigStats) / 8));
-    HIPCHK(hipGetLastError());
+    if (nsig() == 0) return FFCZ_OK;
     std::vector<int> oneblock;
     for (auto& kv : bp->by_mc) {
       const int lg = kv.first;
@@ -2532,9 +2665,9 @@ struct SigRun {
     }
     // the one-block classes run their whole correction on their own stream, beside the tiled
     // rounds (and, in a mixed batch, beside the grouped members: the set-up's end on s does
-    // not wait for them)
+    // not wait for them); with no tiled classes there is nothing to run beside
     hipStream_t sb = s;
-    if (!oneblock.empty() && side) {
+    if (!oneblock.empty() && side && !(tiled.empty() && bp->groups.empty())) {
       HIPCHK(hipEventRecord(fork, s));
       HIPCHK(hipStreamWaitEvent(side, fork, 0));
       sb = side;
@@ -2546,40 +2679,44 @@ struct SigRun {
       if (o.verify_fp64) HIPCHK(go(SIG_VERIFY, lg, sb));
     }
     // tiled classes: set-up, eps0 and the first forward column pass
-    for (int lg : tiled) {
-      if (kinds[lg].first) {
-        HIPCHK(go(SIGT_CHIRP, lg, s));
-        HIPCHK(go(SIGT_BCOL, lg, s));
-        HIPCHK(go(SIGT_BROW, lg, s));
-      }
-      HIPCHK(go(SIGT_EPS0, lg, s));
-      HIPCHK(go(SIGT_CIN, lg, s));
-    }
+    HIPCHK(across(lanes, [&](int lg, hipStream_t st) {
+      hipError_t e = hipSuccess;
+      if (kinds.at(lg).first)
+        for (int m : {(int)SIGT_CHIRP, (int)SIGT_BCOL, (int)SIGT_BROW})
+          if ((e = go(m, lg, st)) != hipSuccess) return e;
+      if ((e = go(SIGT_EPS0, lg, st)) != hipSuccess) return e;
+      return go(SIGT_CIN, lg, st);
+    }));
     return FFCZ_OK;
   }
 
-  // one chunk of rounds of every tiled class, on st
-  hipError_t enqueue_chunk(hipStream_t st) const {
+  // one chunk of rounds of class lg on st
+  hipError_t chunk_of(int lg, hipStream_t st) const {
+    const bool b = kinds.at(lg).first, p2 = kinds.at(lg).second;
+    int nct = 0, nrt = 0;
+    sig_tiles(lg, &nct, &nrt);
+    const int nb = (int)bp->by_mc.at(lg).size();
     hipError_t e = hipSuccess;
-    for (int r = 0; r < chunk && e == hipSuccess; ++r) {
-      for (int lg : tiled) {
-        const bool b = kinds.at(lg).first, p2 = kinds.at(lg).second;
-        if (b && (e = go(SIGT_RMUL, lg, st)) != hipSuccess) return e;
-        if (p2 && (e = go(SIGT_RCHECK, lg, st)) != hipSuccess) return e;
-        if (b && (e = go(SIGT_CCHECK, lg, st)) != hipSuccess) return e;
-        int nct = 0, nrt = 0;
-        sig_tiles(lg, &nct, &nrt);
-        const int nb = (int)bp->by_mc.at(lg).size();
-        hipLaunchKernelGGL(sig_ctl_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
-                           (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
-                           (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
-                           (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt, max_iter, (int32_t)fixed);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (b && (e = go(SIGT_RMULI, lg, st)) != hipSuccess) return e;
-        if ((e = go(SIGT_CSPAT, lg, st)) != hipSuccess) return e;
-      }
+    for (int r = 0; r < chunk; ++r) {
+      if (b && (e = go(SIGT_RMUL, lg, st)) != hipSuccess) return e;
+      if (p2 && (e = go(SIGT_RCHECK, lg, st)) != hipSuccess) return e;
+      if (b && (e = go(SIGT_CCHECK, lg, st)) != hipSuccess) return e;
+      hipLaunchKernelGGL(sig_ctl_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
+                         (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
+                         (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
+                         (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt, max_iter, (int32_t)fixed);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if (b && (e = go(SIGT_RMULI, lg, st)) != hipSuccess) return e;
+      if ((e = go(SIGT_CSPAT, lg, st)) != hipSuccess) return e;
     }
     return e;
+  }
+
+  // one chunk of rounds of every tiled class, on lanes L (forked and joined here, or already
+  // forked and to be joined by the caller: a captured fork of a forked stream is avoided)
+  hipError_t enqueue_chunk(const SigLanes& L, bool forked = false) const {
+    auto f = [&](int lg, hipStream_t st) { return chunk_of(lg, st); };
+    return forked ? spread(L, f) : across(L, f);
   }
 
   // everything a captured chunk bakes in: the workspace, the members' layout, the cap, the chunk
@@ -2618,7 +2755,7 @@ struct SigRun {
       if (!gexec) {
         HIPCHK(g_streams.ready());
         HIPCHK(hipStreamBeginCapture(g_streams.cap, hipStreamCaptureModeThreadLocal));
-        const hipError_t ce = enqueue_chunk(g_streams.cap);
+        const hipError_t ce = enqueue_chunk(SigLanes{3, {g_streams.cap, g_streams.cap2, g_streams.cap3}});
         hipGraph_t graph = nullptr;
         const hipError_t ee = hipStreamEndCapture(g_streams.cap, &graph);
         if (ce != hipSuccess) {
@@ -2634,7 +2771,7 @@ struct SigRun {
     }
     for (int enq = 0;; enq += chunk) {
       if (gexec) HIPCHK(hipGraphLaunch(gexec, s));
-      else HIPCHK(enqueue_chunk(s));
+      else HIPCHK(enqueue_chunk(lanes));
       HIPCHK(hipMemcpyAsync(hs, ws + bp->off_sstats, sizeof(SigStats) * ns, hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
       if (all_done(hs)) break;
@@ -2643,23 +2780,23 @@ struct SigRun {
     return FFCZ_OK;
   }
 
-  // the tiled classes' outputs and verification on s, then s waits for the one-block classes
+  // the tiled classes' outputs and verification, then s waits for the one-block classes
   int32_t end() {
-    for (int lg : tiled) {
-      HIPCHK(go(SIGT_Y, lg, s));
-      if (!o.verify_fp64) continue;
-      HIPCHK(go(SIGT_VCOL, lg, s));
-      HIPCHK(go(SIGT_VROW, lg, s));
-      if (kinds[lg].first) HIPCHK(go(SIGT_VCOL2, lg, s));
+    HIPCHK(across(lanes, [&](int lg, hipStream_t st) {
+      hipError_t e = go(SIGT_Y, lg, st);
+      if (e != hipSuccess || !o.verify_fp64) return e;
+      if ((e = go(SIGT_VCOL, lg, st)) != hipSuccess) return e;
+      if ((e = go(SIGT_VROW, lg, st)) != hipSuccess) return e;
+      if (kinds.at(lg).first && (e = go(SIGT_VCOL2, lg, st)) != hipSuccess) return e;
       int nct = 0, nrt = 0;
       sig_tiles(lg, &nct, &nrt);
       const int nb = (int)bp->by_mc.at(lg).size();
-      hipLaunchKernelGGL(sig_vstats_kernel, dim3((unsigned)nb), dim3(256), 0, s, (const SigDesc*)(ws + bp->off_desc),
+      hipLaunchKernelGGL(sig_vstats_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
                          (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
                          (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
                          (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt);
-      HIPCHK(hipGetLastError());
-    }
+      return hipGetLastError();
+    }));
     return rejoin();
   }
 
@@ -2674,26 +2811,31 @@ struct SigRun {
   ~SigRun() { (void)rejoin(); }
 };
 
-int32_t run_sigs(const BatchPlan& bp, const ffcz_instance* inst, const double* mus, int32_t max_iter,
-                 const ffcz_options& o, char* ws, hipStream_t s, HostBuf& hsig, HostBuf& hstate) {
+int32_t run_sigs(const BatchPlan& bp, int32_t max_iter, const ffcz_options& o, char* ws, hipStream_t s,
+                 const std::map<int, int>& first, HostBuf& hstate) {
   if (bp.sig_ids.empty()) return FFCZ_OK;
   HIPCHK(g_streams.ready());
   SigRun sr;
-  int32_t r = sr.begin(bp, inst, mus, max_iter, o, ws, s, g_streams.side2, g_streams.fork2, g_streams.join2, hsig);
+  int32_t r = sr.begin(bp, max_iter, o, ws, first, SigLanes{3, {s, g_streams.lane1, g_streams.lane2}},
+                       g_streams.side2, g_streams.fork2, g_streams.join2);
   if (r != FFCZ_OK) return r;
   r = sr.loop(hstate);
   if (r != FFCZ_OK) return r;
   return sr.end();
 }
 
-int32_t collect_sigs(const BatchPlan& bp, const ffcz_instance* inst, const double* mus, const ffcz_options& o,
-                     char* ws, hipStream_t s, ffcz_stats* stats, int32_t* status) {
+// dmu: the members' margins on the device, where the host does not have them yet (else null).
+int32_t collect_sigs(const BatchPlan& bp, const ffcz_instance* inst, std::vector<double>& mus, const double* dmu,
+                     const ffcz_options& o, char* ws, hipStream_t s, ffcz_stats* stats, int32_t* status) {
   const int ns = (int)bp.sig_ids.size();
   if (ns == 0) return FFCZ_OK;
-  HIPCHK(g_host_misc.reserve(sizeof(SigStats) * ns));
+  HIPCHK(g_host_misc.reserve(sizeof(SigStats) * ns + sizeof(double) * mus.size()));
   SigStats* h = (SigStats*)g_host_misc.p;
+  double* hmu = (double*)(h + ns);
   HIPCHK(hipMemcpyAsync(h, ws + bp.off_sstats, sizeof(SigStats) * ns, hipMemcpyDeviceToHost, s));
+  if (dmu) HIPCHK(hipMemcpyAsync(hmu, dmu, sizeof(double) * mus.size(), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  if (dmu) mus.assign(hmu, hmu + mus.size());
   for (int k = 0; k < ns; ++k) {
     const int id = bp.sig_ids[k];
     const SigStats& g = h[k];
@@ -2776,13 +2918,13 @@ struct SideJoin {
 // verification on the side stream, joined before return.
 template <typename T>
 int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::vector<double>& mus,
-                    int32_t max_iter, const ffcz_options& o, char* w, hipStream_t s, ffcz_stats* stats,
-                    std::vector<int32_t>& status) {
+                    int32_t max_iter, const ffcz_options& o, char* w, hipStream_t s, const std::map<int, int>& first,
+                    ffcz_stats* stats, std::vector<int32_t>& status) {
   for (size_t g = 0; g < bp.groups.size(); ++g) {
     int32_t r = pretune_group<T>(bp.gplans[g], w + bp.goff[g], s);
     if (r != FFCZ_OK) return r;
   }
-  int32_t r = pretune_sigs(bp, inst, mus.data(), o, w, s, g_host_sig);
+  int32_t r = pretune_sigs(bp, o, w, s, first);
   if (r != FFCZ_OK) return r;
   HIPCHK(g_streams.ready());
   const hipStream_t s1 = g_streams.side;
@@ -2792,7 +2934,8 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
   side.s = s;
   side.s1 = s1;
   SigRun sr;      // declared after the join: its own stream joins s1 first
-  r = sr.begin(bp, inst, mus.data(), max_iter, o, w, s1, g_streams.side2, g_streams.fork2, g_streams.join2, g_host_sig);
+  r = sr.begin(bp, max_iter, o, w, first, SigLanes{2, {s1, g_streams.lane1, nullptr}}, g_streams.side2,
+               g_streams.fork2, g_streams.join2);
   if (r != FFCZ_OK) return r;
   HIPCHK(hipEventRecord(g_streams.ready1d, s1));
   // the groups' set-up on s; their instance and margin arrays live as long as the runs
@@ -2811,12 +2954,19 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
     if (r != FFCZ_OK) return r;
   }
   HIPCHK(hipStreamWaitEvent(s, g_streams.ready1d, 0));
-  // one chunk of everything: the groups on a, the tiled 1D classes on b, forked from and joined into a
-  auto enqueue_all = [&](hipStream_t a, hipStream_t b) -> hipError_t {
+  // one chunk of everything: the groups on a, the tiled 1D classes on b and b2, forked from and joined into a
+  auto enqueue_all = [&](hipStream_t a, hipStream_t b, hipStream_t b2) -> hipError_t {
     hipError_t e = hipEventRecord(g_streams.cfork, a);
     if (e == hipSuccess) e = hipStreamWaitEvent(b, g_streams.cfork, 0);
+    const SigLanes L{2, {b, b2, nullptr}};
+    const bool two = sr.lanes_used(L) > 1;
+    if (e == hipSuccess && two) e = hipStreamWaitEvent(b2, g_streams.cfork, 0);
     for (size_t g = 0; g < ng && e == hipSuccess; ++g) e = gr[g]->enqueue_chunk(a);
-    if (e == hipSuccess) e = sr.enqueue_chunk(b);
+    if (e == hipSuccess) e = sr.enqueue_chunk(L, true);
+    if (e == hipSuccess && two) {
+      e = hipEventRecord(g_streams.ljoin[0], b2);
+      if (e == hipSuccess) e = hipStreamWaitEvent(a, g_streams.ljoin[0], 0);
+    }
     if (e == hipSuccess) e = hipEventRecord(g_streams.cjoin, b);
     if (e == hipSuccess) e = hipStreamWaitEvent(a, g_streams.cjoin, 0);
     return e;
@@ -2833,7 +2983,7 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
     gexec = sig_graphs().find(key);
     if (!gexec) {
       HIPCHK(hipStreamBeginCapture(g_streams.cap, hipStreamCaptureModeThreadLocal));
-      const hipError_t ce = enqueue_all(g_streams.cap, g_streams.cap2);
+      const hipError_t ce = enqueue_all(g_streams.cap, g_streams.cap2, g_streams.cap3);
       hipGraph_t graph = nullptr;
       const hipError_t ee = hipStreamEndCapture(g_streams.cap, &graph);
       if (ce != hipSuccess) {
@@ -2859,7 +3009,7 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
   const int chunk = o.graph_chunk > 0 ? o.graph_chunk : 4;
   for (int enq = 0;; enq += chunk) {
     if (gexec) HIPCHK(hipGraphLaunch(gexec, s));
-    else HIPCHK(enqueue_all(s, s1));
+    else HIPCHK(enqueue_all(s, s1, g_streams.lane1));
     HIPCHK(hipMemcpyAsync(hb, w + bp.off_sstats, sizeof(SigStats) * bp.sig_ids.size(), hipMemcpyDeviceToHost, s));
     for (size_t g = 0; g < ng; ++g)
       HIPCHK(hipMemcpyAsync(hb + hoff[g], gr[g]->c.st(), sizeof(DevState) * (size_t)bp.gplans[g].B,
@@ -3486,7 +3636,7 @@ int32_t ffcz_suggest_margin(int32_t dtype, int32_t ndim, const int64_t* shape, c
   hipStream_t s = (hipStream_t)stream;
   double* slots = (double*)ws;
   const int nsl = ulp_slots(N);
-  const MarginJob job{(const float*)x, N, delta_f};
+  const MarginJob job{(const float*)x, N, delta_f, 0};
   hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)nsl), dim3(256), 0, s, job, (const MarginJob*)nullptr, slots);
   HIPCHK(hipGetLastError());
   hipLaunchKernelGGL(margin_kernel, dim3(1), dim3(256), 0, s, (const double*)slots, job,
@@ -3948,56 +4098,50 @@ int32_t ffcz_correct_batched(int32_t dtype, int32_t count, const ffcz_instance* 
   }
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
-  // margins: per instance (FP32: suggested from x, all members in one launch; FP64: 2^-16)
-  std::vector<double> mus(count, o.margin_rel);
-  if (!(o.margin_rel > 0.0) && count > 0) {
-    std::vector<int64_t> Ns(count);
-    for (int i = 0; i < count; ++i) {
-      int64_t sq[3];
-      const int nd = squeeze(inst[i].ndim, inst[i].shape, sq);
-      int64_t N = 1;
-      for (int d = 0; d < nd; ++d) N *= sq[d];
-      Ns[i] = N;
-    }
-    if (dtype == FFCZ_F64) {
-      for (int i = 0; i < count; ++i) mus[i] = std::ldexp(1.0, -16);
-    } else {
-      HIPCHK(g_host_misc.reserve(sizeof(MarginJob) * count + sizeof(double) * count));
-      MarginJob* hj = (MarginJob*)g_host_misc.p;
-      double* hmu = (double*)(hj + count);
-      int64_t nmax = 1;
-      for (int i = 0; i < count; ++i) {
-        hj[i] = MarginJob{(const float*)inst[i].x_orig, Ns[i], inst[i].delta_f};
-        nmax = std::max(nmax, Ns[i]);
-      }
-      MarginJob* dj = (MarginJob*)(w + bp.off_mjobs);
-      double* dpart = (double*)(w + bp.off_msum);
-      double* dmu = dpart + (size_t)count * kUlpSlots;
-      HIPCHK(hipMemcpyAsync(dj, hj, sizeof(MarginJob) * count, hipMemcpyHostToDevice, s));
-      const unsigned bx = (unsigned)ulp_slots(nmax);
-      for (int c0 = 0; c0 < count; c0 += 65535) {  // grid y holds at most 65535 fields
-        const int nc = std::min(65535, count - c0);
-        hipLaunchKernelGGL(ulp_part_kernel, dim3(bx, (unsigned)nc), dim3(256), 0, s, MarginJob{},
-                           (const MarginJob*)dj + c0, dpart + (size_t)c0 * kUlpSlots);
-        HIPCHK(hipGetLastError());
-      }
-      hipLaunchKernelGGL(margin_kernel, dim3((unsigned)count), dim3(256), 0, s, (const double*)dpart, MarginJob{},
-                         (const MarginJob*)dj, (int)FFCZ_F32, dmu, (DevState*)nullptr);
+  // margins: per instance (FP32: suggested from x, all members in one launch; FP64: 2^-16).  The
+  // thresholds of 1D members are set on the device; a batch without groups reads the margins
+  // back with the statistics.
+  const bool derive = !(o.margin_rel > 0.0) && dtype == FFCZ_F32 && count > 0;
+  std::vector<double> mus(count, o.margin_rel > 0.0 ? o.margin_rel : std::ldexp(1.0, -16));
+  double* const dmu = (double*)(w + bp.off_msum) + (size_t)count * kUlpSlots;
+  std::map<int, int> first;
+  if (count > 0) {
+    r = sig_stage(bp, count, inst, derive ? nullptr : mus.data(), w, s, g_host_sig, first);
+    if (r != FFCZ_OK) return r;
+  }
+  if (derive) {
+    int64_t nmax = 1;
+    for (int i = 0; i < count; ++i) nmax = std::max(nmax, ((const MarginJob*)g_host_sig.p)[i].n);
+    const MarginJob* dj = (const MarginJob*)(w + bp.off_mjobs);
+    double* dpart = (double*)(w + bp.off_msum);
+    const unsigned bx = (unsigned)ulp_slots(nmax);
+    for (int c0 = 0; c0 < count; c0 += 65535) {  // grid y holds at most 65535 fields
+      const int nc = std::min(65535, count - c0);
+      hipLaunchKernelGGL(ulp_part_kernel, dim3(bx, (unsigned)nc), dim3(256), 0, s, MarginJob{}, dj + c0,
+                         dpart + (size_t)c0 * kUlpSlots);
       HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(hmu, dmu, sizeof(double) * count, hipMemcpyDeviceToHost, s));
+    }
+    hipLaunchKernelGGL(margin_kernel, dim3((unsigned)count), dim3(256), 0, s, (const double*)dpart, MarginJob{}, dj,
+                       (int)FFCZ_F32, dmu, (DevState*)nullptr, (SigDesc*)(w + bp.off_desc));
+    HIPCHK(hipGetLastError());
+    if (!bp.groups.empty()) {
+      HIPCHK(g_host_misc.reserve(sizeof(double) * count));
+      HIPCHK(hipMemcpyAsync(g_host_misc.p, dmu, sizeof(double) * count, hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
-      for (int i = 0; i < count; ++i) mus[i] = hmu[i];
+      memcpy(mus.data(), g_host_misc.p, sizeof(double) * count);
     }
   }
+  r = sig_tables(bp, w, s);
+  if (r != FFCZ_OK) return r;
   std::vector<int32_t> status(count, FFCZ_OK);
   if (!bp.sig_ids.empty() && !bp.groups.empty()) {
-    r = dtype == FFCZ_F32 ? mixed_batch<float>(bp, inst, mus, max_iter, o, w, s, stats, status)
-                          : mixed_batch<double>(bp, inst, mus, max_iter, o, w, s, stats, status);
+    r = dtype == FFCZ_F32 ? mixed_batch<float>(bp, inst, mus, max_iter, o, w, s, first, stats, status)
+                          : mixed_batch<double>(bp, inst, mus, max_iter, o, w, s, first, stats, status);
     if (r != FFCZ_OK) return r;
   } else {
-    r = pretune_sigs(bp, inst, mus.data(), o, w, s, g_host_sig);
+    r = pretune_sigs(bp, o, w, s, first);
     if (r != FFCZ_OK) return r;
-    r = run_sigs(bp, inst, mus.data(), max_iter, o, w, s, g_host_sig, g_host_sigstate);
+    r = run_sigs(bp, max_iter, o, w, s, first, g_host_sigstate);
     if (r != FFCZ_OK) return r;
     for (size_t g = 0; g < bp.groups.size(); ++g) {
       const Plan& p = bp.gplans[g];
@@ -4019,7 +4163,7 @@ int32_t ffcz_correct_batched(int32_t dtype, int32_t count, const ffcz_instance* 
       }
     }
   }
-  r = collect_sigs(bp, inst, mus.data(), o, w, s, stats, status.data());
+  r = collect_sigs(bp, inst, mus, derive && bp.groups.empty() ? dmu : nullptr, o, w, s, stats, status.data());
   if (r != FFCZ_OK) return r;
   if (stats)
     for (int i = 0; i < count; ++i) stats[i].status = status[i];
