@@ -80,11 +80,12 @@ typedef struct {
   /* Optional device int64 array of max_iter + 1 entries: violation count of
    * every check (entry k = check after k projection blocks; unused entries 0). */
   int64_t* viol_per_round;
-  /* Rounds enqueued between two host polls of the device done-flag (0 = 4). */
+  /* Rounds enqueued between two host polls of the device done-flag (0 = 4), where
+   * the loop is polled in chunks (use_graph = 0 and ffcz_correct_noalloc). */
   int32_t graph_chunk;
-  /* 1 (default): the chunk of rounds between two polls is captured once in a
-   * hipGraph (cached per shape, workspace and output pointers) and replayed on
-   * the caller's stream; 0: plain launches.  Ignored while profiling. */
+  /* 1 (default): the device posts every check's outcome to pinned host memory and
+   * the host enqueues the next round while the passes after the check still run;
+   * 0: chunks of rounds with one poll per chunk.  Identical results. */
   int32_t use_graph;
   /* Batched 1D members whose power-of-two work length Mc (Mc = L for a
    * power-of-two L >= 4, else the Bluestein length >= L + floor(L/2)) is at least
@@ -170,8 +171,7 @@ int32_t ffcz_suggest_margin(int32_t dtype, int32_t ndim, const int64_t* shape, c
  *   opts    NULL for defaults
  *   workspace / workspace_bytes  device scratch of ffcz_workspace_bytes() bytes
  *   stats   NULL or a host struct filled on return
- * The call blocks on the host once per graph_chunk rounds to read the device
- * done-flag, and at the end for the statistics and the status.  With
+ * The call blocks on the host until the loop has ended (see use_graph), and at the end for the statistics and the status.  With
  * fixed_iterations = 1, stats = NULL and verify_fp64 = 0 nothing is reported,
  * so the call is fully asynchronous (no host synchronisation) and returns
  * FFCZ_OK once the work is enqueued; non-finite input is then not detected
@@ -427,10 +427,10 @@ size_t ffcz_batched_workspace_bytes(int32_t dtype, int32_t count, const ffcz_ins
  * either one block per signal with the whole loop inside one launch (its work
  * buffer in LDS when it fits, see resident_1d), beside everything else, or as
  * tiled passes (many blocks per signal); tiled_1d_lg describes the choice.
- * The rounds of the grouped members and of the tiled 1D classes are enqueued
- * in chunks, each chunk one hipGraph replay (both kinds as parallel branches
- * of one graph when the batch has both), with one host poll of the done-flags
- * per chunk; the call returns when every member is finished and verified.
+ * The rounds of every group and of every tiled 1D class are enqueued as the
+ * device posts its checks (see use_graph), independent classes side by side on
+ * streams of the calling thread; the call returns when every member is finished
+ * and verified.
  * The first call with a new shape or length class may time tile variants and
  * the 1D forms on the call's own data (see ffcz_set_tuning).  Options as in
  * ffcz_correct except that masks and per-round counts are not recorded.

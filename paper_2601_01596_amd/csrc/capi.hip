@@ -19,10 +19,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <map>
 #include <memory>
@@ -787,6 +790,18 @@ __device__ __forceinline__ unsigned long long fold_strided(const unsigned long l
 __device__ __forceinline__ unsigned long long add_u64(unsigned long long a, unsigned long long b) { return a + b; }
 __device__ __forceinline__ unsigned long long max_u64(unsigned long long a, unsigned long long b) { return a > b ? a : b; }
 
+// What a control kernel tells the host after a check: one word per instance (or 1D signal) in
+// pinned host memory, (call tag << 40) | (done << 32) | checks completed.  w null: nothing.
+struct Post {
+  unsigned long long* w;
+  unsigned long long tag;
+};
+__device__ __forceinline__ void post_check(const Post& p, int64_t i, int checks, int done) {
+  if (p.w)
+    __hip_atomic_store(p.w + i, (p.tag << 40) | ((unsigned long long)done << 32) | (unsigned)checks, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Per-round control, one block per instance: sum the x-pass partials into
 // v_k, fold the spatial-clip partials of the z-pass that produced the checked
 // iterate into the totals, and decide on the device whether the loop stops
@@ -795,7 +810,7 @@ __device__ __forceinline__ unsigned long long max_u64(unsigned long long a, unsi
 __global__ void __launch_bounds__(1024) ctl_kernel(DevState* st0, unsigned long long* viol0, int64_t vstride,
                                                    const unsigned long long* xpart, int64_t xbpi,
                                                    const unsigned long long* zpart, int64_t zbpi,
-                                                   int64_t ibpi) {
+                                                   int64_t ibpi, Post post) {
   __shared__ unsigned long long rx[16], rz[16];
   const int64_t b = blockIdx.x;
   DevState* st = st0 + b;
@@ -837,6 +852,7 @@ __global__ void __launch_bounds__(1024) ctl_kernel(DevState* st0, unsigned long 
     }
     if (stop) st->done = 1;
     else st->round = k + 1;
+    post_check(post, b, k + 1, stop);
   }
 }
 
@@ -888,6 +904,7 @@ struct Ctx {
   void* facc = nullptr;
   // pointwise bounds: the (Re, Im) bound pairs laid out as Z (null: the scalar bounds)
   const void* pD = nullptr;
+  Post post{nullptr, 0};  // where the control kernel tells the host of a check
   DevState* st() const { return (DevState*)(ws + p->off_state); }
   unsigned long long* viol() const { return (unsigned long long*)(ws + p->off_viol); }
   void* twT() const { return ws + p->off_twT; }
@@ -901,7 +918,7 @@ struct Ctx {
 
 hipError_t launch_ctl(const Ctx& c, unsigned long long* viol, int64_t vstride) {
   hipLaunchKernelGGL(ctl_kernel, dim3((unsigned)c.p->B), dim3(1024), 0, c.s, c.st(), viol, vstride, c.part(Ctx::PX),
-                     c.p->xbpi, c.part(Ctx::PZ), c.p->zbpi, c.p->ibpi);
+                     c.p->xbpi, c.part(Ctx::PZ), c.p->zbpi, c.p->ibpi, c.post);
   return hipGetLastError();
 }
 
@@ -1182,71 +1199,132 @@ thread_local HostBuf g_host_state, g_host_init, g_host_misc;
 // allocated or freed per call on a short-lived thread (hipHostFree synchronises the device)
 thread_local HostBuf g_host_sig, g_host_sigstate;
 
-// Private streams (default priority): one to capture graphs on, one for the
-// 1D members of a batch, which run beside the grouped members.
+// Private streams (default priority) for the 1D members of a batch, which run beside the
+// grouped members and beside one another.
 struct Streams {
-  // cap, cap2: capture (the second for a graph's parallel branch); side: the 1D members of a
-  // mixed batch; side2: the 1D members that run one block each
-  // lane1, lane2 (cap3 under capture): 1D length classes beside those on the class lane 0
-  hipStream_t cap = nullptr, cap2 = nullptr, cap3 = nullptr, side = nullptr, side2 = nullptr, lane1 = nullptr,
-              lane2 = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr, fork2 = nullptr, join2 = nullptr, ready1d = nullptr, looped = nullptr,
-             cfork = nullptr, cjoin = nullptr, lfork = nullptr, ljoin[2] = {nullptr, nullptr};
+  // side: the 1D members of a mixed batch; side2: the 1D members that run one block each;
+  // lane1, lane2: 1D length classes beside those on the class lane 0
+  hipStream_t side = nullptr, side2 = nullptr, lane1 = nullptr, lane2 = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr, fork2 = nullptr, join2 = nullptr, lfork = nullptr,
+             ljoin[2] = {nullptr, nullptr};
   ~Streams() {
-    for (hipStream_t q : {cap, cap2, cap3, side, side2, lane1, lane2})
+    for (hipStream_t q : {side, side2, lane1, lane2})
       if (q) (void)hipStreamDestroy(q);
-    for (hipEvent_t ev : {fork, join, fork2, join2, ready1d, looped, cfork, cjoin, lfork, ljoin[0], ljoin[1]})
+    for (hipEvent_t ev : {fork, join, fork2, join2, lfork, ljoin[0], ljoin[1]})
       if (ev) (void)hipEventDestroy(ev);
   }
   hipError_t ready() {
     hipError_t e = hipSuccess;
-    for (hipStream_t* q : {&cap, &cap2, &cap3, &side, &side2, &lane1, &lane2})
+    for (hipStream_t* q : {&side, &side2, &lane1, &lane2})
       if (e == hipSuccess && !*q) e = hipStreamCreateWithFlags(q, hipStreamNonBlocking);
-    for (hipEvent_t* ev : {&fork, &join, &fork2, &join2, &ready1d, &looped, &cfork, &cjoin, &lfork, &ljoin[0],
-                           &ljoin[1]})
+    for (hipEvent_t* ev : {&fork, &join, &fork2, &join2, &lfork, &ljoin[0], &ljoin[1]})
       if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
     return e;
   }
 };
 thread_local Streams g_streams;
 
-// Instantiated graphs of a chunk of rounds, keyed by everything the launches capture.
-struct GraphKey {
-  std::vector<int64_t> k;
-  bool operator<(const GraphKey& o) const { return k < o.k; }
+// The words the control kernels post checks to (Post): pinned host memory of the calling
+// thread, a new tag for every call, so that a word of an earlier call is never taken for this
+// one's.
+struct Posts {
+  unsigned long long* p = nullptr;
+  size_t n = 0;
+  unsigned long long tag = 0;
+  ~Posts() {
+    if (p) (void)hipHostFree(p);
+  }
+  hipError_t start(size_t words) {
+    tag = tag == 0xffffff ? 1 : tag + 1;
+    if (words <= n) return hipSuccess;
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    n = 0;
+    const hipError_t e = hipHostMalloc((void**)&p, words * sizeof(*p), hipHostMallocMapped | hipHostMallocCoherent);
+    if (e != hipSuccess) return e;
+    n = words;
+    memset(p, 0, words * sizeof(*p));
+    return hipSuccess;
+  }
+  Post at(size_t i) const { return Post{p + i, tag}; }
 };
-struct GraphCache {
-  std::map<GraphKey, hipGraphExec_t> m;
-  std::vector<GraphKey> order;
-  ~GraphCache() {
-    for (auto& kv : m) (void)hipGraphExecDestroy(kv.second);
-  }
-  hipGraphExec_t find(const GraphKey& key) {
-    auto it = m.find(key);
-    return it == m.end() ? nullptr : it->second;
-  }
-  void put(const GraphKey& key, hipGraphExec_t g) {
-    if (m.size() >= 16) {
-      auto old = order.front();
-      order.erase(order.begin());
-      auto it = m.find(old);
-      if (it != m.end()) {
-        (void)hipGraphExecDestroy(it->second);
-        m.erase(it);
+thread_local Posts g_posts;
+
+// Rounds of one loop, enqueued by drive() on one stream: words [w0, w0 + n) of g_posts tell
+// how far its instances are.
+struct RoundTask {
+  hipStream_t s;
+  size_t w0, n;
+  std::function<hipError_t(int)> round;  // enqueue round r
+  int enq = 0;
+  bool done = false;
+};
+
+// Run loops to their end: round r is enqueued once check r - 1 has been posted and some instance
+// goes on.  The passes between a check and the next round (the inverse transforms and the
+// spatial clip) run meanwhile, so the device does not wait for the host, and the only work past
+// the last check is those passes' early returns.  (Chunks of 4 rounds replayed as a hipGraph with
+// one poll per chunk, measured before: 64^3 FP64, 4 rounds, 238 us, of which 3 rounds of early
+// returns 30 us, two polls 30 us; a new workspace paid for a capture.)
+int32_t drive(std::vector<RoundTask>& tasks, int32_t max_iter) {
+  auto last_query = std::chrono::steady_clock::now();
+  for (;;) {
+    bool all = true, moved = false;
+    for (RoundTask& t : tasks) {
+      if (t.done) continue;
+      int low = INT_MAX;
+      for (size_t i = 0; i < t.n; ++i) {
+        const unsigned long long v = __atomic_load_n(g_posts.p + t.w0 + i, __ATOMIC_RELAXED);
+        if ((v >> 40) != g_posts.tag) low = 0;
+        else if (!((v >> 32) & 1)) low = std::min(low, (int)(v & 0xffffffffu));
+      }
+      if (low == INT_MAX) {
+        t.done = true;
+        continue;
+      }
+      all = false;
+      if (t.enq <= low && t.enq <= max_iter) {
+        HIPCHK(t.round(t.enq));
+        ++t.enq;
+        moved = true;
       }
     }
-    m[key] = g;
-    order.push_back(key);
+    if (all) return FFCZ_OK;
+    if (moved) continue;
+    const auto now = std::chrono::steady_clock::now();
+    if (now - last_query > std::chrono::microseconds(200)) {
+      // a stream that failed, or drained without posting, ends the wait
+      last_query = now;
+      bool idle = true;
+      for (RoundTask& t : tasks) {
+        if (t.done) continue;
+        const hipError_t e = hipStreamQuery(t.s);
+        if (e == hipErrorNotReady) {
+          (void)hipGetLastError();
+          idle = false;
+        } else if (e != hipSuccess) {
+          return fail(FFCZ_E_HIP, std::string("rounds: ") + hipGetErrorString(e));
+        }
+      }
+      if (idle) {
+        bool stuck = false;
+        for (RoundTask& t : tasks) {
+          if (t.done) continue;
+          bool fresh = true;  // every instance posted the check of the last enqueued round, or is done
+          for (size_t i = 0; i < t.n; ++i) {
+            const unsigned long long v = __atomic_load_n(g_posts.p + t.w0 + i, __ATOMIC_RELAXED);
+            const bool mine = (v >> 40) == g_posts.tag;
+            fresh = fresh && mine && (((v >> 32) & 1) || (int)(v & 0xffffffffu) >= t.enq);
+          }
+          if (!fresh) stuck = true;
+        }
+        if (stuck) return fail(FFCZ_E_HIP, "loop did not report completion (device state inconsistent)");
+      }
+    }
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
   }
-};
-thread_local GraphCache g_graphs;
-// Graphs of the tiled 1D rounds: process-wide (the thread that drives the 1D members of a
-// mixed batch is started per call), behind a mutex.  Never destroyed at exit: the HIP runtime
-// may already be gone when static destructors run.
-std::mutex g_sig_graphs_m;
-GraphCache& sig_graphs() {
-  static GraphCache* c = new GraphCache();
-  return *c;
 }
 
 double bits_to_double(unsigned long long b) {
@@ -1765,25 +1843,12 @@ struct GroupRun {
     return FFCZ_OK;
   }
 
-  // One chunk of rounds on st (the round passes return at entry once the instance is done).
-  hipError_t enqueue_chunk(hipStream_t st) const {
-    Ctx cc{&p, c.ws, st};
-    cc.sacc = c.sacc;
-    cc.facc = c.facc;
-    cc.pD = c.pD;
-    for (int r = 0; r < chunk; ++r) {
-      const hipError_t e = enqueue_round<T>(cc, r, viol, vstr, fmask, smask);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
+  hipError_t round(int r) const { return enqueue_round<T>(c, r, viol, vstr, fmask, smask); }
 
-  // Everything a captured chunk bakes in.
-  GraphKey graph_key() const {
-    return GraphKey{{(int64_t)p.dt, p.nd, p.B, p.n[0], p.n[1], p.n[2], (int64_t)(uintptr_t)c.ws,
-                     (int64_t)(uintptr_t)viol, vstr, (int64_t)(uintptr_t)fmask, (int64_t)(uintptr_t)smask, chunk,
-                     max_iter, p.vy, p.vx, p.vz, (int64_t)(uintptr_t)c.sacc, (int64_t)(uintptr_t)c.facc,
-                     (int64_t)(uintptr_t)c.pD}};
+  // The rounds as a task of drive(), checks posted from word w0 on.
+  RoundTask task(size_t w0) {
+    c.post = g_posts.at(w0);
+    return RoundTask{c.s, w0, (size_t)p.B, [this](int r) { return round(r); }};
   }
 
   // The host copy of the instances' states (the no-allocation form brings its own).
@@ -1793,43 +1858,26 @@ struct GroupRun {
     return FFCZ_OK;
   }
 
-  // The rounds, driven from here: fixed rounds enqueued at once, else chunks (captured once in
-  // a hipGraph unless per-launch timing is on) with one poll of the done-flags per chunk.
+  // The rounds, driven from here: fixed rounds enqueued at once; else round by round as checks are
+  // posted (drive), or, on request and in the no-allocation form, in chunks with one poll of the
+  // done-flags per chunk.
   int32_t loop() {
     const hipStream_t s = c.s;
+    if (o.fixed_iterations) {
+      // exactly max_iter blocks plus the final check: no polling needed
+      for (int r = 0; r <= max_iter; ++r) HIPCHK(round(r));
+      return FFCZ_OK;
+    }
+    if (o.use_graph && !no_alloc) {
+      HIPCHK(g_posts.start((size_t)p.B));
+      std::vector<RoundTask> t{task(0)};
+      return drive(t, max_iter);
+    }
     DevState* hs = nullptr;
     int32_t hr = host_states(&hs);
     if (hr != FFCZ_OK) return hr;
-    if (o.fixed_iterations) {
-      // exactly max_iter blocks plus the final check: no polling needed
-      for (int r = 0; r <= max_iter; ++r) HIPCHK(enqueue_round<T>(c, r, viol, vstr, fmask, smask));
-      return FFCZ_OK;
-    }
-    hipGraphExec_t gexec = nullptr;
-    if (o.use_graph && !g_prof.on && !no_alloc) {
-      const GraphKey key = graph_key();
-      gexec = g_graphs.find(key);
-      if (!gexec) {
-        HIPCHK(g_streams.ready());
-        HIPCHK(hipStreamBeginCapture(g_streams.cap, hipStreamCaptureModeThreadLocal));
-        const hipError_t ce = enqueue_chunk(g_streams.cap);
-        hipGraph_t graph = nullptr;
-        const hipError_t ee = hipStreamEndCapture(g_streams.cap, &graph);
-        if (ce != hipSuccess) {
-          if (graph) (void)hipGraphDestroy(graph);
-          return fail(FFCZ_E_HIP, std::string("capture: ") + hipGetErrorString(ce));
-        }
-        HIPCHK(ee);
-        const hipError_t ie = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        HIPCHK(ie);
-        g_graphs.put(key, gexec);
-      }
-    }
     for (int enq = 0;;) {
-      if (gexec) HIPCHK(hipGraphLaunch(gexec, s));
-      else
-        for (int r = 0; r < chunk; ++r) HIPCHK(enqueue_round<T>(c, enq + r, viol, vstr, fmask, smask));
+      for (int r = 0; r < chunk; ++r) HIPCHK(round(enq + r));
       enq += chunk;
       HIPCHK(hipMemcpyAsync(hs, c.st(), sizeof(DevState) * p.B, hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
@@ -2219,7 +2267,8 @@ int32_t batch_plan(int32_t dt, int32_t count, const ffcz_instance* inst, int32_t
 // checked iterate), record them, and decide whether the signal's loop ends.
 __global__ void __launch_bounds__(256) sig_ctl_kernel(const SigDesc* sig, SigStats* stats, const int32_t* order,
                                                        const unsigned long long* part, int32_t nsig, int32_t ptiles,
-                                                       int32_t nct, int32_t nrt, int32_t max_iter, int32_t fixed) {
+                                                       int32_t nct, int32_t nrt, int32_t max_iter, int32_t fixed,
+                                                       Post post) {
   __shared__ unsigned long long red[3][4];
   const int slot = blockIdx.x;
   if (slot >= nsig) return;
@@ -2273,6 +2322,7 @@ __global__ void __launch_bounds__(256) sig_ctl_kernel(const SigDesc* sig, SigSta
     }
     if (stop) so->done = 1;
     else so->rounds = k + 1;
+    post_check(post, slot, k + 1, stop);
   }
 }
 
@@ -2510,7 +2560,7 @@ hipError_t sig_trial(const BatchPlan& bp, char* ws, const int32_t* ord, int lg, 
     hipLaunchKernelGGL(sig_ctl_kernel, dim3((unsigned)nb), dim3(256), 0, s, (const SigDesc*)(ws + bp.off_desc),
                        (SigStats*)(ws + bp.off_sstats), ord, (const unsigned long long*)(ws + bp.tpart_off.at(lg)),
                        (int32_t)nb, (int32_t)bp.tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt, (int32_t)rounds,
-                       (int32_t)1);
+                       (int32_t)1, Post{nullptr, 0});
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (blue && (e = go(SIGT_RMULI)) != hipSuccess) return e;
     if ((e = go(SIGT_CSPAT)) != hipSuccess) return e;
@@ -2690,45 +2740,45 @@ struct SigRun {
     return FFCZ_OK;
   }
 
-  // one chunk of rounds of class lg on st
-  hipError_t chunk_of(int lg, hipStream_t st) const {
+  // one round of class lg on st, checks posted to post
+  hipError_t round_of(int lg, hipStream_t st, const Post& post) const {
     const bool b = kinds.at(lg).first, p2 = kinds.at(lg).second;
     int nct = 0, nrt = 0;
     sig_tiles(lg, &nct, &nrt);
     const int nb = (int)bp->by_mc.at(lg).size();
     hipError_t e = hipSuccess;
-    for (int r = 0; r < chunk; ++r) {
-      if (b && (e = go(SIGT_RMUL, lg, st)) != hipSuccess) return e;
-      if (p2 && (e = go(SIGT_RCHECK, lg, st)) != hipSuccess) return e;
-      if (b && (e = go(SIGT_CCHECK, lg, st)) != hipSuccess) return e;
-      hipLaunchKernelGGL(sig_ctl_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
-                         (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
-                         (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
-                         (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt, max_iter, (int32_t)fixed);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      if (b && (e = go(SIGT_RMULI, lg, st)) != hipSuccess) return e;
-      if ((e = go(SIGT_CSPAT, lg, st)) != hipSuccess) return e;
-    }
-    return e;
+    if (b && (e = go(SIGT_RMUL, lg, st)) != hipSuccess) return e;
+    if (p2 && (e = go(SIGT_RCHECK, lg, st)) != hipSuccess) return e;
+    if (b && (e = go(SIGT_CCHECK, lg, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(sig_ctl_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
+                       (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
+                       (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
+                       (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt, max_iter, (int32_t)fixed, post);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (b && (e = go(SIGT_RMULI, lg, st)) != hipSuccess) return e;
+    return go(SIGT_CSPAT, lg, st);
   }
 
-  // one chunk of rounds of every tiled class, on lanes L (forked and joined here, or already
-  // forked and to be joined by the caller: a captured fork of a forked stream is avoided)
-  hipError_t enqueue_chunk(const SigLanes& L, bool forked = false) const {
-    auto f = [&](int lg, hipStream_t st) { return chunk_of(lg, st); };
-    return forked ? spread(L, f) : across(L, f);
+  // the rounds of every tiled class as tasks of drive(), checks posted from word w0 on; returns the
+  // first word past them
+  size_t tasks(std::vector<RoundTask>& out, size_t w0) {
+    (void)spread(lanes, [&](int lg, hipStream_t st) {
+      const size_t n = bp->by_mc.at(lg).size();
+      const Post post = g_posts.at(w0);
+      out.push_back(RoundTask{st, w0, n, [this, lg, st, post](int) { return round_of(lg, st, post); }});
+      w0 += n;
+      return hipSuccess;
+    });
+    return w0;
   }
 
-  // everything a captured chunk bakes in: the workspace, the members' layout, the cap, the chunk
-  void key_into(GraphKey& key) const {
-    key.k.insert(key.k.end(), {-1, (int64_t)bp->dt, (int64_t)(uintptr_t)ws, (int64_t)max_iter, (int64_t)fixed,
-                               (int64_t)chunk, (int64_t)nsig()});
-    for (int k = 0; k < nsig(); ++k) {
-      key.k.push_back(bp->sigs[k].L);
-      key.k.push_back(bp->sigs[k].blue);
-      key.k.push_back((int64_t)bp->sig_off[k]);
-    }
-    for (int lg : tiled) key.k.push_back(lg);
+  // one chunk of rounds of every tiled class
+  hipError_t enqueue_chunk() const {
+    return across(lanes, [&](int lg, hipStream_t st) {
+      hipError_t e = hipSuccess;
+      for (int r = 0; r < chunk && e == hipSuccess; ++r) e = round_of(lg, st, Post{nullptr, 0});
+      return e;
+    });
   }
 
   // whether every tiled signal's loop has ended, from a host copy of the signal states
@@ -2739,39 +2789,21 @@ struct SigRun {
     return true;
   }
 
-  // the tiled rounds driven from here: chunks captured once in a hipGraph (process-wide cache)
-  // and replayed, one poll of the done-flags per chunk
+  // the tiled rounds driven from here: round by round as checks are posted, or, on request, in
+  // chunks with one poll of the done-flags per chunk
   int32_t loop(HostBuf& hstate) {
     if (tiled.empty()) return FFCZ_OK;
     const int ns = nsig();
+    if (o.use_graph) {
+      HIPCHK(g_posts.start((size_t)ns));
+      std::vector<RoundTask> t;
+      tasks(t, 0);
+      return drive(t, max_iter);
+    }
     HIPCHK(hstate.reserve(sizeof(SigStats) * ns));
     SigStats* hs = (SigStats*)hstate.p;
-    hipGraphExec_t gexec = nullptr;
-    if (o.use_graph && !g_prof.on) {
-      GraphKey key;
-      key_into(key);
-      std::lock_guard<std::mutex> lk(g_sig_graphs_m);
-      gexec = sig_graphs().find(key);
-      if (!gexec) {
-        HIPCHK(g_streams.ready());
-        HIPCHK(hipStreamBeginCapture(g_streams.cap, hipStreamCaptureModeThreadLocal));
-        const hipError_t ce = enqueue_chunk(SigLanes{3, {g_streams.cap, g_streams.cap2, g_streams.cap3}});
-        hipGraph_t graph = nullptr;
-        const hipError_t ee = hipStreamEndCapture(g_streams.cap, &graph);
-        if (ce != hipSuccess) {
-          if (graph) (void)hipGraphDestroy(graph);
-          return fail(FFCZ_E_HIP, std::string("capture of the 1D rounds: ") + hipGetErrorString(ce));
-        }
-        HIPCHK(ee);
-        const hipError_t ie = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        HIPCHK(ie);
-        sig_graphs().put(key, gexec);
-      }
-    }
     for (int enq = 0;; enq += chunk) {
-      if (gexec) HIPCHK(hipGraphLaunch(gexec, s));
-      else HIPCHK(enqueue_chunk(lanes));
+      HIPCHK(enqueue_chunk());
       HIPCHK(hipMemcpyAsync(hs, ws + bp->off_sstats, sizeof(SigStats) * ns, hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
       if (all_done(hs)) break;
@@ -2797,11 +2829,18 @@ struct SigRun {
                          (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt);
       return hipGetLastError();
     }));
+    lanes.n = 1;  // joined
     return rejoin();
   }
 
-  // s waits for the one-block stream (also on early exits, so no launch outlives the call)
+  // s waits for the other lanes and the one-block stream (also on early exits, so no launch
+  // outlives the call)
   int32_t rejoin() {
+    for (int k = 1; k < lanes.n && lanes.q[k]; ++k) {
+      HIPCHK(hipEventRecord(g_streams.ljoin[k - 1], lanes.q[k]));
+      HIPCHK(hipStreamWaitEvent(s, g_streams.ljoin[k - 1], 0));
+    }
+    lanes.n = 1;
     if (!side_used) return FFCZ_OK;
     side_used = false;
     HIPCHK(hipEventRecord(join, side));
@@ -2910,12 +2949,11 @@ struct SideJoin {
 
 
 // A batch of 1D and grouped members, driven from the calling thread.  Everything is tuned
-// first, with nothing else running.  Then the 1D set-up runs on a side stream (its one-block
-// classes on a second one, beside everything else) while the groups' set-up runs on the caller's
-// stream; every chunk of rounds is one hipGraph holding each group's chunk and every tiled 1D
-// class's chunk as two parallel branches, replayed with one poll of all done-flags per chunk;
-// last, the groups' closing passes on the caller's stream and the tiled classes' outputs and
-// verification on the side stream, joined before return.
+// first, with nothing else running.  Then the 1D set-up runs on side streams (its one-block
+// classes on one of their own, beside everything else) while the groups' set-up runs on the
+// caller's stream; the rounds of every group and of every tiled 1D class advance on their own as
+// their checks are posted; last, the groups' closing passes on the caller's stream and the tiled
+// classes' outputs and verification on the side streams, joined before return.
 template <typename T>
 int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::vector<double>& mus,
                     int32_t max_iter, const ffcz_options& o, char* w, hipStream_t s, const std::map<int, int>& first,
@@ -2937,7 +2975,6 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
   r = sr.begin(bp, max_iter, o, w, first, SigLanes{2, {s1, g_streams.lane1, nullptr}}, g_streams.side2,
                g_streams.fork2, g_streams.join2);
   if (r != FFCZ_OK) return r;
-  HIPCHK(hipEventRecord(g_streams.ready1d, s1));
   // the groups' set-up on s; their instance and margin arrays live as long as the runs
   const size_t ng = bp.groups.size();
   std::vector<std::vector<ffcz_instance>> gis(ng);
@@ -2953,79 +2990,51 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
                          nullptr, nullptr);
     if (r != FFCZ_OK) return r;
   }
-  HIPCHK(hipStreamWaitEvent(s, g_streams.ready1d, 0));
-  // one chunk of everything: the groups on a, the tiled 1D classes on b and b2, forked from and joined into a
-  auto enqueue_all = [&](hipStream_t a, hipStream_t b, hipStream_t b2) -> hipError_t {
-    hipError_t e = hipEventRecord(g_streams.cfork, a);
-    if (e == hipSuccess) e = hipStreamWaitEvent(b, g_streams.cfork, 0);
-    const SigLanes L{2, {b, b2, nullptr}};
-    const bool two = sr.lanes_used(L) > 1;
-    if (e == hipSuccess && two) e = hipStreamWaitEvent(b2, g_streams.cfork, 0);
-    for (size_t g = 0; g < ng && e == hipSuccess; ++g) e = gr[g]->enqueue_chunk(a);
-    if (e == hipSuccess) e = sr.enqueue_chunk(L, true);
-    if (e == hipSuccess && two) {
-      e = hipEventRecord(g_streams.ljoin[0], b2);
-      if (e == hipSuccess) e = hipStreamWaitEvent(a, g_streams.ljoin[0], 0);
-    }
-    if (e == hipSuccess) e = hipEventRecord(g_streams.cjoin, b);
-    if (e == hipSuccess) e = hipStreamWaitEvent(a, g_streams.cjoin, 0);
-    return e;
-  };
-  hipGraphExec_t gexec = nullptr;
-  if (o.use_graph && !g_prof.on) {
-    GraphKey key{{-2}};
+  if (o.use_graph || o.fixed_iterations) {
+    // every group's and every tiled class's rounds side by side; fixed rounds end by their
+    // control kernels too
+    size_t words = bp.sig_ids.size(), w0 = 0;
+    for (const Plan& gp : bp.gplans) words += (size_t)gp.B;
+    HIPCHK(g_posts.start(words));
+    std::vector<RoundTask> t;
     for (size_t g = 0; g < ng; ++g) {
-      const GraphKey gk = gr[g]->graph_key();
-      key.k.insert(key.k.end(), gk.k.begin(), gk.k.end());
+      t.push_back(gr[g]->task(w0));
+      w0 += (size_t)bp.gplans[g].B;
     }
-    sr.key_into(key);
-    std::lock_guard<std::mutex> lk(g_sig_graphs_m);
-    gexec = sig_graphs().find(key);
-    if (!gexec) {
-      HIPCHK(hipStreamBeginCapture(g_streams.cap, hipStreamCaptureModeThreadLocal));
-      const hipError_t ce = enqueue_all(g_streams.cap, g_streams.cap2, g_streams.cap3);
-      hipGraph_t graph = nullptr;
-      const hipError_t ee = hipStreamEndCapture(g_streams.cap, &graph);
-      if (ce != hipSuccess) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return fail(FFCZ_E_HIP, std::string("capture of the batch rounds: ") + hipGetErrorString(ce));
+    sr.tasks(t, w0);
+    r = drive(t, max_iter);
+    if (r != FFCZ_OK) return r;
+  } else {
+    // chunks of everything, with one poll of every group's states and the signal states per chunk
+    size_t hbytes = sizeof(SigStats) * bp.sig_ids.size();
+    std::vector<size_t> hoff(ng);
+    for (size_t g = 0; g < ng; ++g) {
+      hoff[g] = hbytes;
+      hbytes += sizeof(DevState) * (size_t)bp.gplans[g].B;
+    }
+    HIPCHK(g_host_sigstate.reserve(hbytes));
+    char* hb = (char*)g_host_sigstate.p;
+    const int chunk = o.graph_chunk > 0 ? o.graph_chunk : 4;
+    for (int enq = 0;; enq += chunk) {
+      for (size_t g = 0; g < ng; ++g)
+        for (int k = 0; k < chunk; ++k) HIPCHK(gr[g]->round(enq + k));
+      HIPCHK(sr.enqueue_chunk());
+      HIPCHK(hipMemcpyAsync(hb, w + bp.off_sstats, sizeof(SigStats) * bp.sig_ids.size(), hipMemcpyDeviceToHost, s1));
+      for (size_t g = 0; g < ng; ++g)
+        HIPCHK(hipMemcpyAsync(hb + hoff[g], gr[g]->c.st(), sizeof(DevState) * (size_t)bp.gplans[g].B,
+                              hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s1));
+      HIPCHK(hipStreamSynchronize(s));
+      bool all = sr.all_done((const SigStats*)hb);
+      for (size_t g = 0; g < ng && all; ++g) {
+        const DevState* hs = (const DevState*)(hb + hoff[g]);
+        for (int64_t b = 0; b < bp.gplans[g].B; ++b) all = all && hs[b].done;
       }
-      HIPCHK(ee);
-      const hipError_t ie = hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(graph);
-      HIPCHK(ie);
-      sig_graphs().put(key, gexec);
+      if (all) break;
+      if (enq > max_iter + 2 * chunk + 2) return fail(FFCZ_E_HIP, "batch did not report completion");
     }
   }
-  // host copies of every group's states and of the signal states, polled once per chunk
-  size_t hbytes = sizeof(SigStats) * bp.sig_ids.size();
-  std::vector<size_t> hoff(ng);
-  for (size_t g = 0; g < ng; ++g) {
-    hoff[g] = hbytes;
-    hbytes += sizeof(DevState) * (size_t)bp.gplans[g].B;
-  }
-  HIPCHK(g_host_sigstate.reserve(hbytes));
-  char* hb = (char*)g_host_sigstate.p;
-  const int chunk = o.graph_chunk > 0 ? o.graph_chunk : 4;
-  for (int enq = 0;; enq += chunk) {
-    if (gexec) HIPCHK(hipGraphLaunch(gexec, s));
-    else HIPCHK(enqueue_all(s, s1, g_streams.lane1));
-    HIPCHK(hipMemcpyAsync(hb, w + bp.off_sstats, sizeof(SigStats) * bp.sig_ids.size(), hipMemcpyDeviceToHost, s));
-    for (size_t g = 0; g < ng; ++g)
-      HIPCHK(hipMemcpyAsync(hb + hoff[g], gr[g]->c.st(), sizeof(DevState) * (size_t)bp.gplans[g].B,
-                            hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    bool all = sr.all_done((const SigStats*)hb);
-    for (size_t g = 0; g < ng && all; ++g) {
-      const DevState* hs = (const DevState*)(hb + hoff[g]);
-      for (int64_t b = 0; b < bp.gplans[g].B; ++b) all = all && hs[b].done;
-    }
-    if (all) break;
-    if (enq > max_iter + 2 * chunk + 2) return fail(FFCZ_E_HIP, "batch did not report completion");
-  }
-  // the tiled classes' end on s1 (after the loop), the groups' ends on s
-  HIPCHK(hipEventRecord(g_streams.looped, s));
-  HIPCHK(hipStreamWaitEvent(s1, g_streams.looped, 0));
+  // the tiled classes' end on their lanes, the groups' ends on s
   r = sr.end();
   if (r != FFCZ_OK) return r;
   for (size_t g = 0; g < ng; ++g) {
