@@ -85,7 +85,7 @@ hipError_t launch_sig(int iodt, int mode, int lgMc, const void* args, int nsig, 
 int sig_rows_per_tile(int tdt, int lgMc) {
   const int MA = 1 << ((lgMc + 1) / 2), MB = (1 << lgMc) / MA;
   const int PA = MA / pick_E(MA), PB = MB / pick_E(MB);
-  const int NT = imin3(512, MA * PB, MB * PA);
+  const int NT = imin3(sig_tile_lanes((int64_t)1 << lgMc), MA * PB, MB * PA);
   (void)tdt;
   return NT / PA;
 }
@@ -1202,20 +1202,22 @@ thread_local HostBuf g_host_sig, g_host_sigstate;
 // Private streams (default priority) for the 1D members of a batch, which run beside the
 // grouped members and beside one another.
 struct Streams {
-  // side: the 1D members of a mixed batch; side2: the 1D members that run one block each;
-  // lane1, lane2: 1D length classes beside those on the class lane 0
-  hipStream_t side = nullptr, side2 = nullptr, lane1 = nullptr, lane2 = nullptr;
+  // side: the 1D members of a mixed batch (else a lane); side2: the 1D members that run one block
+  // each; lane1: 1D length classes beside those on the class lane 0.  With the caller's stream
+  // these are four, the hardware queues of a process: streams past that share a queue and
+  // wait for one another.
+  hipStream_t side = nullptr, side2 = nullptr, lane1 = nullptr;
   hipEvent_t fork = nullptr, join = nullptr, fork2 = nullptr, join2 = nullptr, lfork = nullptr,
              ljoin[2] = {nullptr, nullptr};
   ~Streams() {
-    for (hipStream_t q : {side, side2, lane1, lane2})
+    for (hipStream_t q : {side, side2, lane1})
       if (q) (void)hipStreamDestroy(q);
     for (hipEvent_t ev : {fork, join, fork2, join2, lfork, ljoin[0], ljoin[1]})
       if (ev) (void)hipEventDestroy(ev);
   }
   hipError_t ready() {
     hipError_t e = hipSuccess;
-    for (hipStream_t* q : {&side, &side2, &lane1, &lane2})
+    for (hipStream_t* q : {&side, &side2, &lane1})
       if (e == hipSuccess && !*q) e = hipStreamCreateWithFlags(q, hipStreamNonBlocking);
     for (hipEvent_t* ev : {&fork, &join, &fork2, &join2, &lfork, &ljoin[0], &ljoin[1]})
       if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
@@ -2493,7 +2495,7 @@ int32_t sig_tables(const BatchPlan& bp, char* ws, hipStream_t s) {
 // otherwise classes below 2^kSigTiledMinLg run one block per signal, classes above 2^16 run
 // tiled, and the ones between take the tuner's decision for (architecture, data type, work
 // length, power-of-two bucket of the class's signal count, kinds of length): variant 0 is the
-// default rule (tiled from 2^15), variant 1 the other form.
+// default rule (tiled from 2^14), variant 1 the other form.
 constexpr int kSigTuneMaxLg = 16;
 std::string sig_tune_key(const BatchPlan& bp, int lg) {
   const std::vector<int>& ids = bp.by_mc.at(lg);
@@ -2506,7 +2508,7 @@ std::string sig_tune_key(const BatchPlan& bp, int lg) {
            bp.dt == FFCZ_F32 ? "f32" : "f64", lg, n, blue ? "b" : "", p2 ? "p" : "");
   return buf;
 }
-bool sig_default_tiled(int lg) { return lg >= 15; }
+bool sig_default_tiled(int lg) { return lg >= 14; }
 
 // The decision for class lg without timing (the table's entry, else the default rule).
 int32_t sig_class_tiled(const BatchPlan& bp, const ffcz_options& o, int lg, hipStream_t s, bool* tiled) {
@@ -2540,15 +2542,12 @@ hipError_t sig_trial(const BatchPlan& bp, char* ws, const int32_t* ord, int lg, 
                      (unsigned long long*)(ws + bp.off_sstats), (int64_t)(ns * sizeof(SigStats) / 8));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (!tiled) {
-    if ((e = go(SIG_SETUP)) != hipSuccess) return e;
-    return go(resident && sig_res_fits(bp.dt, lg) ? SIG_RUNL : SIG_RUN);
-  }
   bool blue = false, p2 = false;
   for (int k : bp.by_mc.at(lg)) (bp.sigs[k].blue ? blue : p2) = true;
   if (blue)
     for (int m : {(int)SIGT_CHIRP, (int)SIGT_BCOL, (int)SIGT_BROW})
       if ((e = go(m)) != hipSuccess) return e;
+  if (!tiled) return go(resident && sig_res_fits(bp.dt, lg) ? SIG_RUNL : SIG_RUN);
   if ((e = go(SIGT_EPS0)) != hipSuccess) return e;
   if ((e = go(SIGT_CIN)) != hipSuccess) return e;
   int nct = 0, nrt = 0;
@@ -2642,6 +2641,31 @@ struct SigRun {
     return sig_launch<float>(bp->dt, mode, lg, *bp, ws, ord, nb, max_iter, fixed, st);
   }
 
+  // the chirp and the spectra of its conjugate, tiled (Bluestein lengths)
+  hipError_t setup_tables(int lg, hipStream_t st) const {
+    hipError_t e = hipSuccess;
+    if (kinds.at(lg).first)
+      for (int m : {(int)SIGT_CHIRP, (int)SIGT_BCOL, (int)SIGT_BROW})
+        if ((e = go(m, lg, st)) != hipSuccess) return e;
+    return e;
+  }
+
+  // the FP64 verification of the members' outputs, tiled
+  hipError_t verify_tiled(int lg, hipStream_t st) const {
+    hipError_t e = go(SIGT_VCOL, lg, st);
+    if (e != hipSuccess) return e;
+    if ((e = go(SIGT_VROW, lg, st)) != hipSuccess) return e;
+    if (kinds.at(lg).first && (e = go(SIGT_VCOL2, lg, st)) != hipSuccess) return e;
+    int nct = 0, nrt = 0;
+    sig_tiles(lg, &nct, &nrt);
+    const int nb = (int)bp->by_mc.at(lg).size();
+    hipLaunchKernelGGL(sig_vstats_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
+                       (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
+                       (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
+                       (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt);
+    return hipGetLastError();
+  }
+
   int lanes_used(const SigLanes& L) const { return std::min<int>(L.n, (int)tiled.size()); }
 
   // f(class, stream) for every tiled class, classes spread over the lanes by their work (entries
@@ -2704,14 +2728,10 @@ struct SigRun {
       bool is_tiled = false;
       int32_t tr = sig_class_tiled(*bp, o, lg, s, &is_tiled);
       if (tr != FFCZ_OK) return tr;
-      if (!is_tiled) {
-        oneblock.push_back(lg);
-        continue;
-      }
-      tiled.push_back(lg);
       bool b = false, p2 = false;
       for (int k : kv.second) (bp->sigs[k].blue ? b : p2) = true;
       kinds[lg] = {b, p2};
+      (is_tiled ? tiled : oneblock).push_back(lg);
     }
     // the one-block classes run their whole correction on their own stream, beside the tiled
     // rounds (and, in a mixed batch, beside the grouped members: the set-up's end on s does
@@ -2724,16 +2744,20 @@ struct SigRun {
       side_used = true;
     }
     for (int lg : oneblock) {
-      HIPCHK(go(SIG_SETUP, lg, sb));
+      // the loop in one launch; set-up and verification (FP64, in memory) tiled where those passes
+      // exist: one block for them took 45 + 72 us of a single signal's call at Mc = 2^14
+      const bool t = lg >= kSigTiledMinLg;
+      if (t) HIPCHK(setup_tables(lg, sb));
+      else HIPCHK(go(SIG_SETUP, lg, sb));
       HIPCHK(go(o.resident_1d && sig_res_fits(bp->dt, lg) ? SIG_RUNL : SIG_RUN, lg, sb));
-      if (o.verify_fp64) HIPCHK(go(SIG_VERIFY, lg, sb));
+      if (!o.verify_fp64) continue;
+      if (t) HIPCHK(verify_tiled(lg, sb));
+      else HIPCHK(go(SIG_VERIFY, lg, sb));
     }
     // tiled classes: set-up, eps0 and the first forward column pass
     HIPCHK(across(lanes, [&](int lg, hipStream_t st) {
-      hipError_t e = hipSuccess;
-      if (kinds.at(lg).first)
-        for (int m : {(int)SIGT_CHIRP, (int)SIGT_BCOL, (int)SIGT_BROW})
-          if ((e = go(m, lg, st)) != hipSuccess) return e;
+      hipError_t e = setup_tables(lg, st);
+      if (e != hipSuccess) return e;
       if ((e = go(SIGT_EPS0, lg, st)) != hipSuccess) return e;
       return go(SIGT_CIN, lg, st);
     }));
@@ -2815,19 +2839,8 @@ struct SigRun {
   // the tiled classes' outputs and verification, then s waits for the one-block classes
   int32_t end() {
     HIPCHK(across(lanes, [&](int lg, hipStream_t st) {
-      hipError_t e = go(SIGT_Y, lg, st);
-      if (e != hipSuccess || !o.verify_fp64) return e;
-      if ((e = go(SIGT_VCOL, lg, st)) != hipSuccess) return e;
-      if ((e = go(SIGT_VROW, lg, st)) != hipSuccess) return e;
-      if (kinds.at(lg).first && (e = go(SIGT_VCOL2, lg, st)) != hipSuccess) return e;
-      int nct = 0, nrt = 0;
-      sig_tiles(lg, &nct, &nrt);
-      const int nb = (int)bp->by_mc.at(lg).size();
-      hipLaunchKernelGGL(sig_vstats_kernel, dim3((unsigned)nb), dim3(256), 0, st, (const SigDesc*)(ws + bp->off_desc),
-                         (SigStats*)(ws + bp->off_sstats), order() + first.at(lg),
-                         (const unsigned long long*)(ws + bp->tpart_off.at(lg)), (int32_t)nb,
-                         (int32_t)bp->tpart_tiles.at(lg), (int32_t)nct, (int32_t)nrt);
-      return hipGetLastError();
+      const hipError_t e = go(SIGT_Y, lg, st);
+      return e != hipSuccess || !o.verify_fp64 ? e : verify_tiled(lg, st);
     }));
     lanes.n = 1;  // joined
     return rejoin();
@@ -2855,7 +2868,7 @@ int32_t run_sigs(const BatchPlan& bp, int32_t max_iter, const ffcz_options& o, c
   if (bp.sig_ids.empty()) return FFCZ_OK;
   HIPCHK(g_streams.ready());
   SigRun sr;
-  int32_t r = sr.begin(bp, max_iter, o, ws, first, SigLanes{3, {s, g_streams.lane1, g_streams.lane2}},
+  int32_t r = sr.begin(bp, max_iter, o, ws, first, SigLanes{3, {s, g_streams.lane1, g_streams.side}},
                        g_streams.side2, g_streams.fork2, g_streams.join2);
   if (r != FFCZ_OK) return r;
   r = sr.loop(hstate);

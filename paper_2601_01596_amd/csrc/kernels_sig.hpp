@@ -98,13 +98,18 @@ enum SigPart : int { SP_VIOL = 0, SP_SCLIP = 1, SP_NONFIN = 2, SP_VMAXF = 3, SP_
 __host__ __device__ constexpr int imin3(int a, int b, int c) { return a < b ? (a < c ? a : c) : (b < c ? b : c); }
 __host__ __device__ constexpr int imax2(int a, int b) { return a > b ? a : b; }
 
-template <typename T, int MA, int MB>
+// Most lanes of a block of the tiled passes: 512, and 128 up to Mc = 2^14, where 512 make only 4
+// tiles per signal and pass.
+__host__ __device__ constexpr int sig_tile_lanes(int64_t Mc) { return Mc <= 16384 ? 128 : 512; }
+
+// NTM: most lanes of a block.
+template <typename T, int MA, int MB, int NTM = sig_tile_lanes((int64_t)MA * MB)>
 struct SigGeom {
   static constexpr int Mc = MA * MB;
   static constexpr int MB_ = MB;
   static constexpr int EA = pick_E(MA), EB = pick_E(MB);
   static constexpr int PA = MA / EA, PB = MB / EB;
-  static constexpr int NTMAX = 512;
+  static constexpr int NTMAX = NTM;
   static constexpr int NT = imin3(NTMAX, MA * PB, MB * PA);
   static constexpr int CC = NT / PB;  // columns per column tile
   static constexpr int RR = NT / PA;  // rows per row tile
@@ -136,8 +141,8 @@ enum SigMode : int {
   SIGT_RCHECK = 9,  // row pass: forward DFT completes, count, clip, inverse  [power of two]
   SIGT_CCHECK = 10, // column pass: X = w c, count, clip, start the inverse DFT [Bluestein]
   SIGT_CSPAT = 11,  // column pass: finish the inverse DFT, s-clip, next forward start
-  SIGT_Y = 12,      // y = x + eps (FP64, clamp); max |y - x| partial
-  SIGT_VCOL = 13,   // verification: column pass of d = y - x (FP64)
+  SIGT_Y = 12,      // y = x + eps (FP64, clamp)
+  SIGT_VCOL = 13,   // verification: column pass of d = y - x (FP64); max |d| partial
   SIGT_VROW = 14,   // verification: row pass (Bluestein: x spectrum of b; else maxima partials)
   SIGT_VCOL2 = 15,  // verification: final column pass, maxima partials         [Bluestein]
   SIG_RUNL = 16,    // as SIG_RUN with the work buffer resident in LDS
@@ -189,16 +194,27 @@ __device__ __forceinline__ double block_max(double v, double* red) {
   return s;
 }
 
+// Most lanes of a block of a mode.  The one-block forms have a signal's whole work to walk
+// through; the resident one (SIG_RUNL) has a CU to itself, so 1024 lanes, which must do with 128
+// registers (loop of a signal with Mc = 2^13 / 2^14 in FP32: 200 / 220 us with 512 lanes and all
+// addresses and twiddles in registers, 101 / 204 us this way).
+__host__ __device__ constexpr int sig_lanes(int mode, int64_t Mc) {
+  return mode == SIG_RUNL ? 1024 : (sig_tiled(mode) ? sig_tile_lanes(Mc) : 512);
+}
+
 template <typename T, typename TIO, int MA, int MB, int MODE>
-__global__ void __launch_bounds__((SigGeom<T, MA, MB>::NT))
+__global__ void __launch_bounds__((SigGeom<T, MA, MB, sig_lanes(MODE, (int64_t)MA * MB)>::NT))
 sig_kernel(SigArgs<T> a) {
-  using G = SigGeom<T, MA, MB>;
+  using G = SigGeom<T, MA, MB, sig_lanes(MODE, (int64_t)MA * MB)>;
+  using GT = SigGeom<T, MA, MB>;  // the tiled passes' rows per tile fix the layout of the row-pass tables
   constexpr int NT = G::NT, CC = G::CC, RR = G::RR;
   constexpr int EA = G::EA, EB = G::EB, PA = G::PA, PB = G::PB;
   constexpr int LPA = G::LPA;
   constexpr int Mc = MA * MB;
   constexpr int BL = 8;
   __shared__ cx<T> lds[sig_lds_entries<G, MODE>()];
+  constexpr int TWA = Sched<MA, EA>::twsize, TWB = Sched<MB, EB>::twsize;
+  __shared__ cx<T> twl[MODE == SIG_RUNL && TWA + TWB > 0 ? TWA + TWB : 1];
   __shared__ unsigned long long red_u[NT / 64 + 1];
   __shared__ double red_d[NT / 64 + 1];
 
@@ -251,7 +267,15 @@ sig_kernel(SigArgs<T> a) {
   const TIO* xs = (const TIO*)sd.x;
   const TIO* xbs = (const TIO*)sd.xb;
   TIO* ys = (TIO*)sd.y;
-  const SigTabs<T> tb = a.tab;
+  SigTabs<T> tb = a.tab;
+  if constexpr (RES) {
+    // the stage twiddles beside the buffer (2 KB at Mc = 2^14)
+    for (int i = t; i < TWA; i += NT) twl[i] = a.tab.twa[i];
+    for (int i = t; i < TWB; i += NT) twl[TWA + i] = a.tab.twb[i];
+    tb.twa = twl;
+    tb.twb = twl + TWA;
+    __syncthreads();
+  }
 
   // ---- column pass: for every column n1, inverse MB-FFT (if INV1), element op at the
   // natural index n = n1 + MA*i (or at k2 = i), forward MB-FFT (if FWD2), times the
@@ -262,7 +286,12 @@ sig_kernel(SigArgs<T> a) {
   auto col_pass = [&](auto INV1c, auto FWD2c, auto in, auto op) {
     constexpr bool INV1 = decltype(INV1c)::value;
     constexpr bool FWD2 = decltype(FWD2c)::value;
-    const int c = t % CC, j = t / CC;
+    // RES: this lane's number afresh in every pass, so that addresses and twiddles of all passes
+    // are not kept in registers through the whole loop (238 registers, 240 spills at 1024 lanes)
+    int tp = t;
+    if constexpr (RES) asm volatile("" : "+v"(tp));
+    const int c = tp % CC, j = tp / CC;
+#pragma unroll 1
     for (int c0 = ctlo * CC; c0 < cthi * CC; c0 += CC) {
       const int n1 = c0 + c;
       cx<T> v[EB];
@@ -298,7 +327,10 @@ sig_kernel(SigArgs<T> a) {
   // inverse MA-FFT times conj(W_Mc^{n1 k2}); coalesced through LDS in both directions.
   auto row_pass = [&](auto INVc, auto op) {
     constexpr bool INV = decltype(INVc)::value;
-    const int rl = t % RR, j = t / RR;
+    int tp = t;
+    if constexpr (RES) asm volatile("" : "+v"(tp));
+    const int rl = tp % RR, j = tp / RR;
+#pragma unroll 1
     for (int r0 = rtlo * RR; r0 < rthi * RR; r0 += RR) {
       const int k2 = r0 + rl;
       cx<T> v[EA];
@@ -313,7 +345,7 @@ sig_kernel(SigArgs<T> a) {
         if constexpr (INV) {
           fft<T, MA, EA, true, 1, CP>(v, rows, tb.twa, rl, j);
 #pragma unroll
-          for (int q = 0; q < EA; ++q) v[q] = cmulc(v[q], tb.tw4r[G::rpos(k2, j + q * PA)]);
+          for (int q = 0; q < EA; ++q) v[q] = cmulc(v[q], tb.tw4r[GT::rpos(k2, j + q * PA)]);
           __syncthreads();  // the last exchange's reads are done before the rows are overwritten
 #pragma unroll
           for (int q = 0; q < EA; ++q) rows[rl * CP + j + q * PA] = v[q];
@@ -356,7 +388,7 @@ sig_kernel(SigArgs<T> a) {
       if constexpr (INV) {
         fft<T, MA, EA, true, 1, LPA>(v, lds, tb.twa, rl, j);
 #pragma unroll
-        for (int q = 0; q < EA; ++q) v[q] = cmulc(v[q], tb.tw4r[G::rpos(k2, j + q * PA)]);
+        for (int q = 0; q < EA; ++q) v[q] = cmulc(v[q], tb.tw4r[GT::rpos(k2, j + q * PA)]);
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < EA; ++q) lrow[j + q * PA] = v[q];
@@ -428,10 +460,10 @@ sig_kernel(SigArgs<T> a) {
     auto store_b = [&](int k2, int k1, cx<T> v) {
       const cx<double> b64{(double)v.re * inv, (double)v.im * inv};
       const cx<float> b32{__double2float_rn(b64.re), __double2float_rn(b64.im)};
-      bt64[G::rpos(k2, k1)] = b64;
-      if (bt32) bt32[G::rpos(k2, k1)] = b32;  // the row layout does not depend on the type
+      bt64[GT::rpos(k2, k1)] = b64;
+      if (bt32) bt32[GT::rpos(k2, k1)] = b32;  // the row layout does not depend on the type
       const int64_t kr = ((int64_t)Mc - (k2 + (int64_t)MB * k1)) & (Mc - 1);
-      const int64_t ri = G::rpos((int)(kr % MB), (int)(kr / MB));
+      const int64_t ri = GT::rpos((int)(kr % MB), (int)(kr / MB));
       if (bt32) ((cx<float>*)sd.btabi)[ri] = b32;
       else ((cx<double>*)sd.btabi)[ri] = b64;
       return v;
@@ -453,7 +485,7 @@ sig_kernel(SigArgs<T> a) {
       }
     };
     auto ident = [&](int, int, cx<T> v) { return v; };
-    auto mulb = [&](int k2, int k1, cx<T> v) { return cmul(v, btab[G::rpos(k2, k1)]); };
+    auto mulb = [&](int k2, int k1, cx<T> v) { return cmul(v, btab[GT::rpos(k2, k1)]); };
     auto fin = [&](int n1, int i, cx<T> c) {
       const int64_t n = n1 + (int64_t)MA * i;
       if (n < L) acc(n, cmul(chirp[n], c));
@@ -464,15 +496,20 @@ sig_kernel(SigArgs<T> a) {
       return v;
     };
     if constexpr (MODE == SIG_VERIFY || MODE == SIGT_VCOL) {
+      double ms = 0.0;
       auto din = [&](int n1, int i) -> cx<T> {
         const int64_t n = n1 + (int64_t)MA * i;
         if (n >= L) return zero;
         const T d = (T)((double)ys[n] - (double)xs[n]);
+        if constexpr (MODE == SIGT_VCOL) ms = fmax(ms, fabs((double)d));
         if (!blue) return cx<T>{d, T(0)};
         return scal(chirp[n], d);
       };
       col_pass(FF{}, TT{}, din, ident);
-      if constexpr (MODE == SIGT_VCOL) return;
+      if constexpr (MODE == SIGT_VCOL) {
+        put_max(SP_VMAXS, ms);
+        return;
+      }
     }
     if constexpr (MODE == SIGT_VROW) {
       if (blue) {
@@ -524,8 +561,8 @@ sig_kernel(SigArgs<T> a) {
     return blue ? scal(chirp[n], e) : cx<T>{e, T(0)};
   };
   auto ident = [&](int, int, cx<T> v) { return v; };
-  auto mulb = [&](int k2, int k1, cx<T> v) { return cmul(v, btab[(int64_t)G::rpos(k2, k1)]); };
-  auto mulbi = [&](int k2, int k1, cx<T> v) { return cmul(v, btabi[(int64_t)G::rpos(k2, k1)]); };
+  auto mulb = [&](int k2, int k1, cx<T> v) { return cmul(v, btab[(int64_t)GT::rpos(k2, k1)]); };
+  auto mulbi = [&](int k2, int k1, cx<T> v) { return cmul(v, btabi[(int64_t)GT::rpos(k2, k1)]); };
   const int64_t Kh = L / 2 + 1;  // half-spectrum entries
   unsigned long long cnt = 0, sc = 0;
   // row: the forward DFT completes here -> count + clip -> inverse row FFT (power of two)
@@ -660,13 +697,8 @@ sig_kernel(SigArgs<T> a) {
     return;
   }
   if constexpr (MODE == SIGT_Y) {
-    double ms = 0.0;
-    for (int64_t n = n_lo + t; n < n_hi; n += NT) {
-      const TIO yv = closing_clamp<TIO>(round_io<TIO>((double)xs[n] + (double)eps[n]), xs[n], Eb);
-      ys[n] = yv;
-      ms = fmax(ms, fabs((double)yv - (double)xs[n]));
-    }
-    put_max(SP_VMAXS, ms);
+    for (int64_t n = n_lo + t; n < n_hi; n += NT)
+      ys[n] = closing_clamp<TIO>(round_io<TIO>((double)xs[n] + (double)eps[n]), xs[n], Eb);
     return;
   }
 }
