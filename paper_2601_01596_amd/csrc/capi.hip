@@ -1340,6 +1340,11 @@ __global__ void zero_u64_kernel(unsigned long long* p, int64_t n) {
   if (i < n) p[i] = 0ull;
 }
 
+__global__ void zero_u32_kernel(uint32_t* p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0u;
+}
+
 // ---------------------------------------------------------------------------
 // Plan tuner.  Each loop pass of a plan (y-forward/inverse, x-pass, last-axis
 // pass) has a few variants: tilings that compute bit-identical results and
@@ -3449,8 +3454,11 @@ HuffLayout huff_layout(int64_t n, int64_t nalpha, int64_t nbits) {
 // Workspace: minmax partials, the frequency table, lengths, codes, block offsets, totals and
 // the decoder's tables.
 struct HuffWs {
-  size_t off_mm, off_counts, off_len, off_code, off_boff, off_tot, off_tab, off_sorted, bytes;
+  size_t off_mm, off_counts, off_code, off_boff, off_tot, off_tab, off_sorted, bytes;
 };
+// Whether a symbol stream starts on the 16-byte boundary that the kernels' vector accesses take.
+int huff_vec(const void* p) { return ((uintptr_t)p & 15) == 0 ? 1 : 0; }
+
 HuffWs huff_ws(int64_t n, int64_t nalpha) {
   HuffWs W;
   size_t off = 0;
@@ -3458,8 +3466,6 @@ HuffWs huff_ws(int64_t n, int64_t nalpha) {
   off = align_up(off + 16 * 1024, 256);
   W.off_counts = off;
   off = align_up(off + 8 * (size_t)nalpha, 256);
-  W.off_len = off;
-  off = align_up(off + (size_t)nalpha, 256);
   W.off_code = off;
   off = align_up(off + 4 * (size_t)nalpha, 256);
   const int64_t nblk = (n + kHuffBlockSyms - 1) / kHuffBlockSyms;
@@ -3467,12 +3473,33 @@ HuffWs huff_ws(int64_t n, int64_t nalpha) {
   off = align_up(off + 8 * (size_t)std::max<int64_t>(1, nblk), 256);
   W.off_tot = off;
   off = align_up(off + 64, 256);
+  // the decoder's upload: a zero status word, the sorted symbols
   W.off_tab = off;
-  off = align_up(off + 3 * 4 * (kHuffMaxLen + 1), 256);
+  off += 16;
   W.off_sorted = off;
   off = align_up(off + 4 * (size_t)nalpha, 256);
   W.bytes = off;
   return W;
+}
+
+// Decode with the lengths compared rounded up to a multiple of 4.
+template <int W>
+hipError_t launch_huff_decode_w(int nl, const HuffDec& d, hipStream_t s) {
+  const dim3 grid((unsigned)((d.nchunks + kHuffDecBlock - 1) / kHuffDecBlock)), block(kHuffDecBlock);
+  const size_t dyn = 4 * (size_t)d.stage + 2 * (size_t)d.nlds;
+  switch ((nl + 3) / 4) {
+    case 1: hipLaunchKernelGGL((huff_decode_kernel<W, 4>), grid, block, dyn, s, d); break;
+    case 2: hipLaunchKernelGGL((huff_decode_kernel<W, 8>), grid, block, dyn, s, d); break;
+    case 3: hipLaunchKernelGGL((huff_decode_kernel<W, 12>), grid, block, dyn, s, d); break;
+    case 4: hipLaunchKernelGGL((huff_decode_kernel<W, 16>), grid, block, dyn, s, d); break;
+    case 5: hipLaunchKernelGGL((huff_decode_kernel<W, 20>), grid, block, dyn, s, d); break;
+    case 6: hipLaunchKernelGGL((huff_decode_kernel<W, 24>), grid, block, dyn, s, d); break;
+    default: hipLaunchKernelGGL((huff_decode_kernel<W, 33>), grid, block, dyn, s, d); break;
+  }
+  return hipGetLastError();
+}
+hipError_t launch_huff_decode(int width, int nl, const HuffDec& d, hipStream_t s) {
+  return width == 1 ? launch_huff_decode_w<1>(nl, d, s) : launch_huff_decode_w<4>(nl, d, s);
 }
 
 // Scratch of ffcz_correct_noalloc (the array is declared at file scope, above): host
@@ -3801,12 +3828,14 @@ int32_t ffcz_huffman_plan(const void* sym, int64_t nsym, int32_t width, void* ws
     if (!ws || ws_bytes < huff_ws(nsym, 0).bytes || ((uintptr_t)ws & 255))
       return fail(FFCZ_E_WORKSPACE, "workspace smaller than ffcz_huffman_workspace_bytes(nsym, 0) or misaligned");
     hipStream_t s = (hipStream_t)stream;
-    const int g = (int)std::min<int64_t>(1024, (nsym + kHuffBlock - 1) / kHuffBlock);
+    const int g = (int)std::min<int64_t>(1024, (nsym + kHuffBlockSyms - 1) / kHuffBlockSyms);
     long long* mm = (long long*)ws;
-    hipLaunchKernelGGL(huff_minmax_kernel, dim3((unsigned)g), dim3(kHuffBlock), 0, s, sym, (int)width, nsym, mm);
+    const auto kern = width == 1 ? huff_minmax_kernel<1> : huff_minmax_kernel<4>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(kHuffBlock), 0, s, sym, nsym, huff_vec(sym), mm);
     HIPCHK(hipGetLastError());
-    std::vector<long long> h(2 * (size_t)g);
-    HIPCHK(hipMemcpyAsync(h.data(), mm, sizeof(long long) * h.size(), hipMemcpyDeviceToHost, s));
+    HIPCHK(g_host_misc.reserve(2 * sizeof(long long) * (size_t)g));
+    const long long* h = (const long long*)g_host_misc.p;
+    HIPCHK(hipMemcpyAsync(g_host_misc.p, mm, 2 * sizeof(long long) * (size_t)g, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     long long lo = h[0], hi = h[1];
     for (int b = 1; b < g; ++b) {
@@ -3844,60 +3873,68 @@ int32_t ffcz_huffman_encode(const void* sym, int64_t nsym, int32_t width, const 
   hd.lo = lo;
   hd.nalpha = nalpha;
   hd.nchunks = (nsym + kHuffChunk - 1) / kHuffChunk;
+  const int vec = huff_vec(sym);
+  const bool w1 = width == 1;
+  HuffTables t;
   std::vector<uint8_t> len;
   if (nsym > 0) {
     // the global frequency table, then the code on the host
     unsigned long long* counts = (unsigned long long*)(w + W.off_counts);
     hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((nalpha + 255) / 256)), dim3(256), 0, s, counts, nalpha);
     HIPCHK(hipGetLastError());
-    const int g = (int)std::min<int64_t>(1024, (nsym + kHuffBlock - 1) / kHuffBlock);
-    hipLaunchKernelGGL(huff_hist_kernel, dim3((unsigned)g), dim3(kHuffBlock), 0, s, sym, (int)width, nsym,
-                       (int64_t)lo, nalpha, counts);
+    // at most one block per CU, of at least two groups (each adds its table at the end)
+    const int64_t group = (int64_t)kHuffHistBlock * kHuffPerLane;
+    const int g = (int)std::max<int64_t>(1, std::min<int64_t>(256, nsym / (2 * group)));
+    const size_t bins = nalpha <= kHuffLdsBins ? 4 * (size_t)nalpha : 0;
+    hipLaunchKernelGGL(w1 ? huff_hist_kernel<1> : huff_hist_kernel<4>, dim3((unsigned)g), dim3(kHuffHistBlock), bins,
+                       s, sym, nsym, (int64_t)lo, nalpha, vec, counts);
     HIPCHK(hipGetLastError());
-    // through pinned staging: the table out, the lengths and codes back (the copies in are
-    // complete at the synchronisation that reads the bit count, before the buffer is reused)
-    HIPCHK(g_host_misc.reserve(8 * (size_t)nalpha));
+    // through pinned staging: the table out, then header, lengths and codes back (copied in by the
+    // synchronisation at the end, before the buffer is reused)
+    HIPCHK(g_host_misc.reserve(std::max(8 * (size_t)nalpha, sizeof(hd) + 5 * (size_t)nalpha + 16)));
     unsigned long long* hcp = (unsigned long long*)g_host_misc.p;
     HIPCHK(hipMemcpyAsync(hcp, counts, 8 * (size_t)nalpha, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    len = huff_lengths(std::vector<unsigned long long>(hcp, hcp + nalpha));
-    const HuffTables t = huff_tables(len);
-    uint8_t* dlen = (uint8_t*)(w + W.off_len);
+    const std::vector<unsigned long long> freq(hcp, hcp + nalpha);
+    len = huff_lengths(freq);
+    t = huff_tables(len);
+    unsigned long long nbits = 0;
+    for (int64_t i = 0; i < nalpha; ++i) nbits += freq[i] * len[i];
+    hd.nbits = (int64_t)nbits;
+  }
+  const HuffLayout L = huff_layout(nsym, nalpha, hd.nbits);
+  if (out_bytes < L.bytes)
+    return fail(FFCZ_E_WORKSPACE, "output smaller than the stream (" + std::to_string(L.bytes) + " bytes)");
+  HIPCHK(g_host_misc.reserve(sizeof(hd) + 5 * (size_t)nalpha + 16));
+  char* const hb = (char*)g_host_misc.p;
+  memcpy(hb, &hd, sizeof(hd));
+  if (nsym > 0) memcpy(hb + L.off_len, len.data(), (size_t)nalpha);
+  HIPCHK(hipMemcpyAsync(o, hb, L.off_len + (nsym > 0 ? (size_t)nalpha : 0), hipMemcpyHostToDevice, s));
+  if (nsym > 0) {
     uint32_t* dcode = (uint32_t*)(w + W.off_code);
-    uint32_t* hcode = (uint32_t*)g_host_misc.p;
-    uint8_t* hlen = (uint8_t*)(hcode + nalpha);
+    uint32_t* hcode = (uint32_t*)(hb + align_up(L.off_len + (size_t)nalpha, 16));
     memcpy(hcode, t.code.data(), 4 * (size_t)nalpha);
-    memcpy(hlen, len.data(), (size_t)nalpha);
-    HIPCHK(hipMemcpyAsync(dlen, hlen, (size_t)nalpha, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(dcode, hcode, 4 * (size_t)nalpha, hipMemcpyHostToDevice, s));
-    // bits per block, block offsets, the total
+    const uint8_t* dlen = (const uint8_t*)(o + L.off_len);
+    // bits per block and block offsets
     const int64_t nblk = (nsym + kHuffBlockSyms - 1) / kHuffBlockSyms;
     unsigned long long* boff = (unsigned long long*)(w + W.off_boff);
     unsigned long long* tot = (unsigned long long*)(w + W.off_tot);
-    hipLaunchKernelGGL(huff_bits_kernel, dim3((unsigned)nblk), dim3(kHuffBlock), 0, s, sym, (int)width, nsym,
-                       (int64_t)lo, (const uint8_t*)dlen, boff);
+    hipLaunchKernelGGL(w1 ? huff_bits_kernel<1> : huff_bits_kernel<4>, dim3((unsigned)nblk), dim3(kHuffBlock), 0, s,
+                       sym, nsym, (int64_t)lo, nalpha, vec, dlen, boff);
     HIPCHK(hipGetLastError());
     hipLaunchKernelGGL(edit_scan_kernel, dim3(1), dim3(1024), 0, s, boff, nblk, tot);
     HIPCHK(hipGetLastError());
-    unsigned long long nbits = 0;
-    HIPCHK(hipMemcpyAsync(&nbits, tot, 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    hd.nbits = (int64_t)nbits;
-    const HuffLayout L = huff_layout(nsym, nalpha, hd.nbits);
-    if (out_bytes < L.bytes) return fail(FFCZ_E_WORKSPACE, "output smaller than the stream (" + std::to_string(L.bytes) + " bytes)");
     const int64_t nwords = (hd.nbits + 31) / 32;
-    hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)(((nwords + 1) / 2 + 255) / 256)), dim3(256), 0, s,
-                       (unsigned long long*)(o + L.off_words), (nwords + 1) / 2);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s,
+                       (uint32_t*)(o + L.off_words), nwords);
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(huff_encode_kernel, dim3((unsigned)nblk), dim3(kHuffBlock), 0, s, sym, (int)width, nsym,
-                       (int64_t)lo, (const uint8_t*)dlen, (const uint32_t*)dcode, (const unsigned long long*)boff,
-                       (unsigned int*)(o + L.off_words), (unsigned long long*)(o + L.off_chunks));
+    hipLaunchKernelGGL(w1 ? huff_encode_kernel<1> : huff_encode_kernel<4>, dim3((unsigned)nblk), dim3(kHuffBlock), 0,
+                       s, sym, nsym, (int64_t)lo, nalpha, vec, dlen, (const uint32_t*)dcode,
+                       (const unsigned long long*)boff, (unsigned int*)(o + L.off_words),
+                       (unsigned long long*)(o + L.off_chunks));
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(o + L.off_len, dlen, (size_t)nalpha, hipMemcpyDeviceToDevice, s));
   }
-  const HuffLayout L = huff_layout(nsym, nalpha, hd.nbits);
-  if (out_bytes < L.bytes) return fail(FFCZ_E_WORKSPACE, "output smaller than the stream");
-  HIPCHK(hipMemcpyAsync(o, &hd, sizeof(hd), hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
   if (used_bytes) *used_bytes = L.bytes;
   return FFCZ_OK;
@@ -3908,9 +3945,13 @@ int32_t ffcz_huffman_decode(const void* in, size_t in_bytes, int32_t width, void
   if (!in || in_bytes < sizeof(HuffHeader)) return fail(FFCZ_E_INVALID, "input too short");
   if ((uintptr_t)in & 15) return fail(FFCZ_E_WORKSPACE, "input must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
-  HuffHeader hd;
-  HIPCHK(hipMemcpyAsync(&hd, in, sizeof(hd), hipMemcpyDeviceToHost, s));
+  // the header and, where they are short, the lengths after it in one read (pinned staging)
+  const size_t head = std::min<size_t>(in_bytes, 16384);
+  HIPCHK(g_host_misc.reserve(16384));
+  HIPCHK(hipMemcpyAsync(g_host_misc.p, in, head, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  HuffHeader hd;
+  memcpy(&hd, g_host_misc.p, sizeof(hd));
   if (hd.magic != kHuffMagic || (hd.width != 1 && hd.width != 4) || hd.nsym < 0 || hd.nalpha < 0 ||
       hd.nalpha > kHuffMaxAlpha || hd.nbits < 0)
     return fail(FFCZ_E_INVALID, "not a stream written by ffcz_huffman_encode");
@@ -3925,13 +3966,16 @@ int32_t ffcz_huffman_decode(const void* in, size_t in_bytes, int32_t width, void
   const HuffWs W = huff_ws(hd.nsym, hd.nalpha);
   if (!ws || ws_bytes < W.bytes || ((uintptr_t)ws & 255))
     return fail(FFCZ_E_WORKSPACE, "workspace smaller than ffcz_huffman_workspace_bytes(nsym, nalpha) or misaligned");
-  // through pinned staging: the lengths out, the decoder's tables back
-  const size_t tab_bytes = 3 * sizeof(uint32_t) * (kHuffMaxLen + 1);
-  HIPCHK(g_host_misc.reserve(std::max<size_t>((size_t)hd.nalpha, tab_bytes + 4 * (size_t)hd.nalpha)));
   const char* ib = (const char*)in;
-  HIPCHK(hipMemcpyAsync(g_host_misc.p, ib + L.off_len, (size_t)hd.nalpha, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  std::vector<uint8_t> len((const uint8_t*)g_host_misc.p, (const uint8_t*)g_host_misc.p + hd.nalpha);
+  std::vector<uint8_t> len((size_t)hd.nalpha);
+  if (L.off_len + (size_t)hd.nalpha <= head) {
+    memcpy(len.data(), (const char*)g_host_misc.p + L.off_len, (size_t)hd.nalpha);
+  } else {
+    HIPCHK(g_host_misc.reserve((size_t)hd.nalpha));
+    HIPCHK(hipMemcpyAsync(g_host_misc.p, ib + L.off_len, (size_t)hd.nalpha, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    memcpy(len.data(), g_host_misc.p, (size_t)hd.nalpha);
+  }
   for (uint8_t l : len)
     if (l > kHuffMaxLen) return fail(FFCZ_E_INVALID, "code length above 32 in the stream");
   const HuffTables t = huff_tables(len);
@@ -3941,30 +3985,57 @@ int32_t ffcz_huffman_decode(const void* in, size_t in_bytes, int32_t width, void
   for (int l = 1; l <= kHuffMaxLen; ++l) kraft += (uint64_t)t.cnt[l] << (kHuffMaxLen - l);
   if (kraft > (1ull << kHuffMaxLen)) return fail(FFCZ_E_INVALID, "code lengths break the Kraft inequality");
   char* w = (char*)ws;
-  uint32_t* tab = (uint32_t*)(w + W.off_tab);
-  uint32_t* htab = (uint32_t*)g_host_misc.p;  // first, cnt, idx, then the sorted symbols
-  memcpy(htab, t.first, sizeof(t.first));
-  memcpy(htab + (kHuffMaxLen + 1), t.cnt, sizeof(t.cnt));
-  memcpy(htab + 2 * (kHuffMaxLen + 1), t.idx, sizeof(t.idx));
-  HIPCHK(hipMemcpyAsync(tab, htab, tab_bytes, hipMemcpyHostToDevice, s));
-  if (!t.sorted.empty()) {
-    memcpy((char*)htab + tab_bytes, t.sorted.data(), 4 * t.sorted.size());
-    HIPCHK(hipMemcpyAsync(w + W.off_sorted, (char*)htab + tab_bytes, 4 * t.sorted.size(), hipMemcpyHostToDevice, s));
+  // a zero status word and the sorted symbols (one upload)
+  const size_t up = W.off_sorted + 4 * t.sorted.size() - W.off_tab;
+  HIPCHK(g_host_misc.reserve(up));
+  memset(g_host_misc.p, 0, W.off_sorted - W.off_tab);
+  if (!t.sorted.empty())
+    memcpy((char*)g_host_misc.p + (W.off_sorted - W.off_tab), t.sorted.data(), 4 * t.sorted.size());
+  HIPCHK(hipMemcpyAsync(w + W.off_tab, g_host_misc.p, up, hipMemcpyHostToDevice, s));
+  unsigned int* bad = (unsigned int*)(w + W.off_tab);
+  HuffDec d;
+  memset(&d, 0, sizeof(d));
+  d.words = (const unsigned int*)(ib + L.off_words);
+  d.nwords = (hd.nbits + 31) / 32;
+  d.chunk_bits = (const unsigned long long*)(ib + L.off_chunks);
+  d.nbits = (unsigned long long)hd.nbits;
+  d.n = hd.nsym;
+  d.lo = hd.lo;
+  d.nchunks = hd.nchunks;
+  d.sorted = (const int32_t*)(w + W.off_sorted);
+  int lmin = 0, lmax = 0;
+  for (int l = 1; l <= kHuffMaxLen; ++l)
+    if (t.cnt[l]) {
+      if (!lmin) lmin = l;
+      lmax = l;
+    }
+  if (!lmin) return fail(FFCZ_E_INVALID, "the stream has symbols but no codes");
+  d.lmin = lmin;
+  d.nlen = lmax - lmin + 1;
+  d.nsorted = (int32_t)t.sorted.size();
+  for (int j = 0; j < 32; ++j) d.top[j] = 0xffffffffu;
+  uint64_t lim = 0;
+  for (int l = lmin; l <= lmax; ++l) {
+    lim = ((uint64_t)t.first[l] + t.cnt[l]) << (32 - l);  // left-justified end of the codes up to length l
+    d.top[l - lmin] = (uint32_t)(lim - 1);
+    d.off[l - lmin] = t.idx[l] - t.first[l];
   }
-  unsigned int* bad = (unsigned int*)(w + W.off_tot);
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, (unsigned long long*)bad, (int64_t)1);
-  HIPCHK(hipGetLastError());
-  const int64_t nch = hd.nchunks;
-  hipLaunchKernelGGL(huff_decode_kernel, dim3((unsigned)((nch + kHuffDecBlock - 1) / kHuffDecBlock)),
-                     dim3(kHuffDecBlock), 0, s,
-                     (const unsigned int*)(ib + L.off_words), (int64_t)((hd.nbits + 31) / 32),
-                     (const unsigned long long*)(ib + L.off_chunks), hd.nsym, (const uint32_t*)tab,
-                     (const uint32_t*)(tab + (kHuffMaxLen + 1)), (const uint32_t*)(tab + 2 * (kHuffMaxLen + 1)),
-                     (const int32_t*)(w + W.off_sorted), (int64_t)hd.lo, (int)width, sym_out, bad);
-  HIPCHK(hipGetLastError());
-  unsigned int hb = 0;
-  HIPCHK(hipMemcpyAsync(&hb, bad, 4, hipMemcpyDeviceToHost, s));
+  // lengths compared: those of the code, and one more that catches the patterns of an incomplete code
+  const int nl = d.nlen + (lim < (1ull << 32) ? 1 : 0);
+  // words staged per block: all that its chunks can hold, at most 48 KB, and no more than twice
+  // what they hold on average (more blocks per CU; a wave with a longer stretch reads memory)
+  const int64_t most = (int64_t)kHuffDecBlock * kHuffChunk * lmax / 32 + 4;
+  const int64_t mean = (hd.nbits / std::max<int64_t>(1, hd.nchunks) + 1) * kHuffDecBlock / 32;
+  d.stage = (int)std::min<int64_t>(12288, std::min(most, 2 * mean + 64));
+  // the symbols in LDS where they fit in 64 KB
+  d.nlds = t.sorted.size() <= 32768 && hd.nalpha <= 65536 ? (int)t.sorted.size() : 0;
+  d.vec = huff_vec(sym_out);
+  d.out = sym_out;
+  d.bad = bad;
+  HIPCHK(launch_huff_decode(width, nl, d, s));
+  HIPCHK(hipMemcpyAsync(g_host_misc.p, bad, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  const unsigned int hb = *(const unsigned int*)g_host_misc.p;
   if (hb) return fail(FFCZ_E_INVALID, "the stream holds a bit pattern that is no code");
   return FFCZ_OK;
 }
