@@ -252,7 +252,8 @@ __host__ __device__ constexpr int pick_rows(int H) { return rows_for_E<T>(H, pic
 // lanes index-fastest and rows moved straight between HBM and registers
 // (elsewhere it runs variant 1, whose rows per block it shares).  Variants 0 and
 // 1 compute identical bits; variants 2 and 3 round differently (other stages,
-// other fused multiply-adds).
+// other fused multiply-adds).  Variant 4, which the tuner does not choose, is the direct form
+// with the bits of variant 0.
 constexpr int kColVariants = 2;
 constexpr int kRowVariants = 4;
 template <typename T>
@@ -265,7 +266,7 @@ __host__ __device__ constexpr int row_E(int H, int v) { return (v == 2 && pick_E
 template <typename T>
 __host__ __device__ constexpr int tile_rows(int H, int v) {
   if (v == 2) return rows_for_E<T>(H, row_E(H, 2));
-  if (v == 3) v = 1;
+  if (v >= 3) v = 1;
   return (pick_rows<T>(H) >> v) < 1 ? 1 : (pick_rows<T>(H) >> v);
 }
 

@@ -674,10 +674,12 @@ __host__ __device__ constexpr int direct_lds_pitch(int H) {
 // (every 8-byte slot taken exactly twice per wave access).  row_kernel stages the
 // whole tile through LDS on the way in and out; the loop pass moves about 40 % less
 // LDS data this way.  Modes: ROW_INIT, ROW_LOOP, ROW_FINAL and the adjoint's
-// ROW_BINIT, ROW_BLOOP, ROW_BFINAL, with row_kernel's formulas; the compiler fuses
-// multiply-adds differently in the two kernels, so results can differ in the last
-// bit (a plan that rounds differently, like radix 8).
-template <int MODE, int H, int ROWS>
+// ROW_BINIT, ROW_BLOOP, ROW_BFINAL.  The C2R and R2C combinations are written as fused
+// multiply-adds with 1/N moved into the R2C, so results can differ from row_kernel's in the last
+// bit (a plan that rounds differently, like radix 8); EX keeps row_kernel's formulas and
+// computes its bits (a few more instructions; a recorded mask is a decision, so calls with masks
+// take this form where nothing else was chosen).
+template <int MODE, int H, int ROWS, bool EX = false>
 __global__ void __launch_bounds__(ROWS * (H / 16), 4) row_direct_kernel(RowArgs<float, float> a) {
   using T = float;
   constexpr int E = 16, P = H / E;
@@ -832,6 +834,12 @@ __global__ void __launch_bounds__(ROWS * (H / 16), 4) row_direct_kernel(RowArgs<
         B.im = T(0);
       }
       const cx<T> w = rtw[k];
+      if constexpr (EX) {
+        const cx<T> sm = A + conjg(B);
+        const cx<T> df = cmulc(A - conjg(B), w);
+        v[q] = cx<T>{sm.re - df.im, sm.im + df.re};
+        continue;
+      }
       const T sre = A.re + B.re, sim = A.im - B.im;
       const T dre = A.re - B.re, dim = A.im + B.im;
       v[q] = cx<T>{__builtin_fmaf(dre, w.im, __builtin_fmaf(-dim, w.re, sre)),
@@ -842,8 +850,13 @@ __global__ void __launch_bounds__(ROWS * (H / 16), 4) row_direct_kernel(RowArgs<
       // ProjectOntoSCube (+ s-mask) on N eps: the bound scaled by N, and 1/N applied by
       // the R2C below
       const T sc = (T)st->inv_n;
-      const T Ep = to_t<T>(st->Ep) / sc;
-      hsc = T(0.5) * sc;
+      const T Ep = EX ? to_t<T>(st->Ep) : to_t<T>(st->Ep) / sc;
+      if constexpr (EX) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) v[q] = scal(v[q], sc);
+      } else {
+        hsc = T(0.5) * sc;
+      }
       if (rec) {
         if (valid) {
 #pragma unroll
@@ -871,8 +884,8 @@ __global__ void __launch_bounds__(ROWS * (H / 16), 4) row_direct_kernel(RowArgs<
     } else {
       // adjoint: g * s-mask and 1/N (in the loop pass, 1/N is applied by the R2C below)
       const T sc = (T)st->inv_n;
-      if constexpr (MODE == ROW_BLOOP) hsc = T(0.5) * sc;
-      const T sv = MODE == ROW_BLOOP ? T(1) : sc;
+      if constexpr (MODE == ROW_BLOOP && !EX) hsc = T(0.5) * sc;
+      const T sv = MODE == ROW_BLOOP && !EX ? T(1) : sc;
 #pragma unroll
       for (int q = 0; q < E; ++q) {
         const int k = j + q * P;
@@ -924,6 +937,13 @@ __global__ void __launch_bounds__(ROWS * (H / 16), 4) row_direct_kernel(RowArgs<
       const cx<T> own = v[(E - q) & (E - 1)];  // lane 0: Z[H - P q], Z[0] for q = 0
       const cx<T> Zm = lane_read((j == 0) ? own : v[E - 1 - q], paddr);
       const cx<T> w = rtw[k];
+      if constexpr (EX) {
+        const cx<T> ev = scal(Zk + conjg(Zm), T(0.5));
+        const cx<T> d = Zk - conjg(Zm);
+        const cx<T> od = cx<T>{d.im * T(0.5), -d.re * T(0.5)};
+        dst[k] = ev + cmul(w, od);
+        continue;
+      }
       const T sre = Zk.re + Zm.re, sim = Zk.im - Zm.im;
       const T dre = Zk.re - Zm.re, dim = Zk.im + Zm.im;
       dst[k] = cx<T>{hsc * __builtin_fmaf(w.im, dre, __builtin_fmaf(w.re, dim, sre)),
