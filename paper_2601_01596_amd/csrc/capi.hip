@@ -35,8 +35,10 @@
 #include "../../include/ffcz.h"
 #include "common.hpp"
 #include "kernels_bounds.hpp"
+#include "kernels_ctl.hpp"
 #include "kernels_edit.hpp"
 #include "kernels_huff.hpp"
+#include "kernels_plane.hpp"
 #include "kernels_sig.hpp"
 #include "launch.hpp"
 #include "sig_dispatch.hpp"
@@ -54,6 +56,8 @@ hipError_t launch_edit_row_f32(int mode, int H, const void* args, int64_t nb, hi
 hipError_t launch_edit_row_f64(int mode, int H, const void* args, int64_t nb, hipStream_t s);
 hipError_t launch_edit_col_f32(int mode, int L, const void* args, int64_t nb, hipStream_t s);
 hipError_t launch_edit_col_f64(int mode, int L, const void* args, int64_t nb, hipStream_t s);
+hipError_t launch_plane_f32(int Ly, int H, const void* args, int64_t nb, hipStream_t s);
+hipError_t launch_plane_f64(int Ly, int H, const void* args, int64_t nb, hipStream_t s);
 hipError_t launch_bounds_row_f32(int mode, int H, int vv, const void* args, int64_t nb, hipStream_t s);
 hipError_t launch_bounds_row_f64(int mode, int H, int vv, const void* args, int64_t nb, hipStream_t s);
 hipError_t launch_bounds_col_f32(int mode, int L, const void* args, int64_t nb, hipStream_t s);
@@ -251,6 +255,7 @@ struct Plan {
   // tile variants of the loop passes (y-forward/inverse, x-pass, last-axis init/loop/final)
   int vy = 0, vx = 0, vz = 0;
   // blocks of each pass per instance (one partial slot per block)
+  bool planes = false;  // the plane pass (kernels_plane.hpp) in place of y-inverse, last axis, y-forward
   int64_t zbpi = 0, ibpi = 0, vzbpi = 0, xbpi = 0, vxbpi = 0;  // ibpi: the init pass (default tiles)
   int64_t pmax = 0;
   size_t off_state = 0, off_ulp = 0, off_viol = 0, off_init = 0, off_part = 0, off_twT = 0, off_tw64 = 0, off_Z = 0,
@@ -334,6 +339,7 @@ void set_variants(Plan& p, int vy, int vx, int vz) {
   p.vy = vy;
   p.vx = vx;
   p.vz = vz;
+  p.planes = false;
   const int64_t outer_x = p.nd == 3 ? p.n[1] : 1;
   const int Rz = row_block_rows(p.dt, p.H, vz), Rz64 = row_block_rows(1, p.H, kVerifyRowPlan);
   p.zbpi = (p.nrows + Rz - 1) / Rz;
@@ -793,18 +799,6 @@ __device__ __forceinline__ unsigned long long fold_strided(const unsigned long l
 __device__ __forceinline__ unsigned long long add_u64(unsigned long long a, unsigned long long b) { return a + b; }
 __device__ __forceinline__ unsigned long long max_u64(unsigned long long a, unsigned long long b) { return a > b ? a : b; }
 
-// What a control kernel tells the host after a check: one word per instance (or 1D signal) in
-// pinned host memory, (call tag << 40) | (done << 32) | checks completed.  w null: nothing.
-struct Post {
-  unsigned long long* w;
-  unsigned long long tag;
-};
-__device__ __forceinline__ void post_check(const Post& p, int64_t i, int checks, int done) {
-  if (p.w)
-    __hip_atomic_store(p.w + i, (p.tag << 40) | ((unsigned long long)done << 32) | (unsigned)checks, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Per-round control, one block per instance: sum the x-pass partials into
 // v_k, fold the spatial-clip partials of the z-pass that produced the checked
 // iterate into the totals, and decide on the device whether the loop stops
@@ -837,25 +831,7 @@ __global__ void __launch_bounds__(1024) ctl_kernel(DevState* st0, unsigned long 
       vz += rz[w];
     }
     const int k = st->round;
-    viol0[b * vstride + k] = vx;
-    if (k == 0) st->v_first = vx;
-    st->v_last = vx;
-    if (k == 0) st->s_guard = vz;
-    else st->s_clipped_total += vz;
-    int stop = 0;
-    if (st->nonfinite) {
-      stop = 1;
-      st->nonfinite_stop = 1;
-    } else if (!st->fixed && vx == 0) {
-      stop = 1;
-      st->converged = 1;
-    } else if (k >= st->max_iter) {
-      stop = 1;
-      st->converged = (vx == 0) ? 1 : 0;
-    }
-    if (stop) st->done = 1;
-    else st->round = k + 1;
-    post_check(post, b, k + 1, stop);
+    record_check(st, k, vx, vz, check_stops(st, k, vx), viol0 + b * vstride, post, b);
   }
 }
 
@@ -1061,6 +1037,38 @@ hipError_t xpass_T(const Ctx& c, const void* src, void* dst, const void* twx, un
                     c.s, c.facc);
 }
 
+// y-inverse, last axis and y-forward of a round in one pass over planes held in LDS.
+template <typename T>
+hipError_t run_planes(const Ctx& c, int r, unsigned long long* viol, int64_t vstride) {
+  const Plan& p = *c.p;
+  const cx<T>* twb = (const cx<T>*)c.twT();
+  PlaneArgs<T> a;
+  memset(&a, 0, sizeof(a));
+  a.A = (cx<T>*)c.A();
+  a.Z = (cx<T>*)c.Z();
+  a.pitch = p.pitch;
+  a.plane = p.plane;
+  a.nplanes = p.n[0];
+  a.twy = twb + p.twy;
+  a.twz = twb + p.twz;
+  a.st = c.st();
+  // the clip counts of two rounds in a row: a block may still read the last round's when another
+  // writes this one's
+  a.part = c.part(r % 2 ? Ctx::PZ : Ctx::PVZ);
+  a.zpart = c.part(r % 2 ? Ctx::PVZ : Ctx::PZ);
+  a.nz = r == 0 ? p.ibpi : p.n[0];
+  a.xpart = c.part(Ctx::PX);
+  a.nx = p.xbpi;
+  a.round = r;
+  a.viol = viol;
+  a.vstride = vstride;
+  a.post = c.post;
+  return p.dt == FFCZ_F32 ? launch_plane_f32(p.Ly, p.H, &a, p.n[0] * p.B, c.s)
+                          : launch_plane_f64(p.Ly, p.H, &a, p.n[0] * p.B, c.s);
+}
+
+// Round r: its check, and the projections up to the next iterate.  With the plane pass the
+// y-forward transform of rounds after the first is the end of the round before.
 template <typename T>
 hipError_t enqueue_round(const Ctx& c, int r, unsigned long long* viol, int64_t vstride, uint8_t* fmask,
                          uint32_t* smask) {
@@ -1071,12 +1079,16 @@ hipError_t enqueue_round(const Ctx& c, int r, unsigned long long* viol, int64_t 
   const void* twx = twb + sizeof(cx<T>) * p.twx;
   hipError_t e;
   if (p.nd == 3) {
-    e = timed(PK_YFWD, r, c.s, [&] {
-      return run_col<T>(p.dt, COL_FWD, p.vy, geom_y(p, p.pitch, p.plane), p, c.Z(), c.A(), twy, c.st(), px, fmask, c.s);
-    });
-    if (e != hipSuccess) return e;
+    if (!p.planes || r == 0) {
+      e = timed(PK_YFWD, r, c.s, [&] {
+        return run_col<T>(p.dt, COL_FWD, p.vy, geom_y(p, p.pitch, p.plane), p, c.Z(), c.A(), twy, c.st(), px, fmask,
+                          c.s);
+      });
+      if (e != hipSuccess) return e;
+    }
     e = timed(PK_XPASS, r, c.s, [&] { return xpass_T<T>(c, c.A(), c.A(), twx, px, fmask); });
     if (e != hipSuccess) return e;
+    if (p.planes) return timed(PK_ZPASS, r, c.s, [&] { return run_planes<T>(c, r, viol, vstride); });
     e = launch_ctl(c, viol, vstride);
     if (e != hipSuccess) return e;
     e = timed(PK_YINV, r, c.s, [&] {
@@ -1557,6 +1569,24 @@ int32_t tune_plan(Plan& p, char* ws, hipStream_t s, bool rec, bool no_time = fal
   return FFCZ_OK;
 }
 
+// Whether a field's rounds run on the plane pass: one block does a whole plane, so a plane must
+// either be small (a few us a block) or come in numbers that keep the chip busy.  20 rounds,
+// separate passes -> plane pass, us (MI355X): planes of 17-35 KB 64 x 64 x 64 FP64 624 -> 421,
+// 4 x 64 x 64 FP32 478 -> 329, 64 x 64 x 128 FP32 642 -> 466; of 66 KB 128^3 FP32 1014 -> 796, 64 x 256 x 64
+// 760 -> 700, but 8 x 256 x 64 551 -> 590; of 131 KB 512 x 64 x 128 1224 -> 1022, 256 x 512 x 64 FP32 1806 -> 1626,
+// 128^3 FP64 1198 -> 1074, but 128 x 512 x 64 FP32 1184 -> 1199, 64 x 256 x 128 FP32 1031 -> 1076 and
+// 32 x 128 x 256 FP32 794 -> 952.
+bool plane_rule(const Plan& p) {
+  const int64_t planes = p.n[0] * p.B;
+  if (p.nd != 3 || planes > p.pmax) return false;
+  if (!(p.dt == FFCZ_F32 ? plane_fits<float>(p.Ly, p.H) : plane_fits<double>(p.Ly, p.H))) return false;
+  const int64_t kb = (int64_t)p.Ly * p.H * (p.dt == FFCZ_F32 ? 8 : 16) / 1024;
+  if (kb > 32 && planes < (kb <= 64 ? 64 : p.dt == FFCZ_F32 ? 256 : 128)) return false;
+  std::lock_guard<std::mutex> g(g_tuner.m);
+  g_tuner.init_locked();
+  return g_tuner.mode == 1;  // the other modes ask for the separate passes' plans
+}
+
 // Tune a group's passes ahead of a mixed batch, before the 1D members start on
 // the side stream (their work would disturb the timings): a neutral state (loop
 // not done, no masks) and the twiddles are written, then tune_plan runs on the
@@ -1849,6 +1879,10 @@ struct GroupRun {
     } else {
       const int32_t tr = tune_plan<T>(p, ws, s, rec, no_alloc);
       if (tr != FFCZ_OK) return tr;
+      if (!rec && plane_rule(p)) {
+        p.planes = true;
+        p.zbpi = p.n[0];
+      }
     }
     HIPCHK(timed(PK_INIT, -1, s, [&] { return row_T<T>(ROW_INIT, c, nullptr, c.Z(), smask); }));
     return FFCZ_OK;
