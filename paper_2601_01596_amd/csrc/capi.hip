@@ -460,12 +460,7 @@ struct TwJobs {
 
 // Stage twiddles exp(-2 pi i m r / (Ns R)) and R2C twiddles exp(-2 pi i k / 2L),
 // evaluated in FP64 with an exactly reduced argument and rounded once.
-// blockIdx.y picks one of two tables (base0/jobs0 or base1/jobs1), so a plan's
-// working-precision and FP64 tables take one launch.
-__global__ void twiddle_kernel(void* base0, TwJobs jobs0, void* base1, TwJobs jobs1) {
-  void* const base = blockIdx.y ? base1 : base0;
-  const TwJobs& jobs = blockIdx.y ? jobs1 : jobs0;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void write_twiddle(void* base, const TwJobs& jobs, int64_t gid) {
   int64_t acc = 0;
   for (int jj = 0; jj < jobs.n; ++jj) {
     const TwJob& jb = jobs.j[jj];
@@ -509,9 +504,9 @@ __global__ void twiddle_kernel(void* base0, TwJobs jobs0, void* base1, TwJobs jo
   }
 }
 
-__global__ void state_init_kernel(DevState* st, int64_t B, const StateInit* arr, StateInit one,
-                                  unsigned long long* viol, int64_t nviol) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Lane t of nthr: the state of instance t, and its share of the words to clear.
+__device__ __forceinline__ void state_init(DevState* st, int64_t B, const StateInit* arr, const StateInit& one,
+                                           unsigned long long* viol, int64_t nviol, int64_t t, int64_t nthr) {
   if (t < B) {
     const StateInit p = arr ? arr[t] : one;
     DevState s;
@@ -538,7 +533,7 @@ __global__ void state_init_kernel(DevState* st, int64_t B, const StateInit* arr,
     s.fp = 1.0 - p.mu;
     st[t] = s;
   }
-  for (int64_t i = t; i < nviol; i += (int64_t)gridDim.x * blockDim.x) viol[i] = 0ull;
+  for (int64_t i = t; i < nviol; i += nthr) viol[i] = 0ull;
 }
 
 // Suggested FP32 margin for a field of N points with bound Delta:
@@ -574,20 +569,18 @@ __device__ inline double ulp2f(float v) {
   return __longlong_as_double(ex << 52);
 }
 
-// Partial sums of ulp(x)^2.  blockIdx.y picks the field (jobs[y], or `one`
-// when jobs is null); its points are cut into nb = ulp_slots(n) contiguous
-// slices of a multiple of 4 points, and block b < nb stores the sum over slice
-// b in part[y * kUlpSlots + b] (blocks past nb have nothing to do).  No
+// Partial sums of ulp(x)^2 of one field: its points are cut into nb = ulp_slots(n)
+// contiguous slices of a multiple of 4 points, and block b < nb (256 lanes) stores the sum
+// over slice b in part[b] (blocks past nb have nothing to do).  No
 // atomics: margin_kernel adds the slots in a fixed order, so mu does not
 // depend on scheduling.  Aligned slices stream 16-byte vectors, four in flight
 // per lane.
-__global__ void __launch_bounds__(256) ulp_part_kernel(MarginJob one, const MarginJob* jobs, double* part) {
+__device__ __forceinline__ void ulp_part(const MarginJob& jb, int64_t b, double* part) {
   __shared__ double red[4];
-  const MarginJob jb = jobs ? jobs[blockIdx.y] : one;
   const int64_t nb = ulp_slots(jb.n);
-  if ((int64_t)blockIdx.x >= nb) return;
+  if (b >= nb) return;
   const int64_t slice = ((jb.n + nb - 1) / nb + 3) & ~int64_t(3);
-  const int64_t lo = std::min<int64_t>(jb.n, (int64_t)blockIdx.x * slice);
+  const int64_t lo = std::min<int64_t>(jb.n, b * slice);
   const int64_t hi = std::min<int64_t>(jb.n, lo + slice);
   const float* x = jb.x;
   double s = 0.0;
@@ -614,7 +607,44 @@ __global__ void __launch_bounds__(256) ulp_part_kernel(MarginJob one, const Marg
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) part[(int64_t)blockIdx.y * kUlpSlots + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x == 0) part[b] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+// One field (jobs null) or field blockIdx.y of several, its slots from part[y * kUlpSlots] on.
+__global__ void __launch_bounds__(256) ulp_part_kernel(MarginJob one, const MarginJob* jobs, double* part) {
+  ulp_part(jobs ? jobs[blockIdx.y] : one, blockIdx.x, part + (int64_t)blockIdx.y * kUlpSlots);
+}
+
+// Everything a call writes or sums before its first pass, side by side in one launch: instance
+// states (nbs blocks; they also clear nzero words), the twiddle tables of both precisions (nbt
+// blocks each) and, where the margin comes from x, the ulp partials of x (the rest).  Three
+// launches of 4-7 us in a row before: 64^3 FP64 156 -> 149 us a correction, 64 x 256 x 128 FP32
+// 230 -> 216, 2048^2 FP32 359 -> 348.
+struct SetupArgs {
+  DevState* st;
+  int64_t B;
+  const StateInit* arr;
+  StateInit one;
+  unsigned long long* zero;
+  int64_t nzero;
+  void* tw[2];
+  TwJobs jobs[2];
+  MarginJob ulp;
+  double* part;
+  int nbs, nbt;
+};
+__global__ void __launch_bounds__(256) setup_kernel(SetupArgs a) {
+  int b = blockIdx.x;
+  if (b < a.nbs) {
+    state_init(a.st, a.B, a.arr, a.one, a.zero, a.nzero, (int64_t)b * 256 + threadIdx.x, (int64_t)a.nbs * 256);
+    return;
+  }
+  b -= a.nbs;
+  if (b < 2 * a.nbt) {
+    const int k = b < a.nbt ? 0 : 1;
+    write_twiddle(a.tw[k], a.jobs[k], (int64_t)(b - k * a.nbt) * 256 + threadIdx.x);
+    return;
+  }
+  ulp_part(a.ulp, b - 2 * a.nbt, a.part);
 }
 
 // One block per field: add its ulp_slots(n) partial sums in a fixed order and
@@ -901,10 +931,20 @@ hipError_t launch_ctl(const Ctx& c, unsigned long long* viol, int64_t vstride) {
   return hipGetLastError();
 }
 
-hipError_t write_twiddles(const Ctx& c) {
+// States (arr, or `one`), cleared words, twiddle tables and, given x, its ulp partials.
+hipError_t run_setup(const Ctx& c, const StateInit* arr, const StateInit& one, unsigned long long* zero, int64_t nzero,
+                     const MarginJob* ulp = nullptr) {
   const Plan& p = *c.p;
+  SetupArgs a;
+  memset(&a, 0, sizeof(a));
+  a.st = c.st();
+  a.B = p.B;
+  a.arr = arr;
+  a.one = one;
+  a.zero = zero;
+  a.nzero = nzero;
   // table 0: working precision (read by the loop kernels); table 1: FP64 (verification)
-  TwJobs jobs[2];
+  TwJobs* const jobs = a.jobs;
   for (int tab = 0; tab < 2; ++tab) {
     memset(&jobs[tab], 0, sizeof(TwJobs));
     jobs[tab].dbl = (tab == 1 || p.dt == FFCZ_F64) ? 1 : 0;
@@ -915,8 +955,18 @@ hipError_t write_twiddles(const Ctx& c) {
     jobs[tab].j[n++] = TwJob{p.twx, p.Lx, p.Ex, 0};
     jobs[tab].n = n;
   }
-  const int nb = (int)((p.twT + 255) / 256);
-  hipLaunchKernelGGL(twiddle_kernel, dim3(nb, 2), dim3(256), 0, c.s, c.twT(), jobs[0], c.tw64(), jobs[1]);
+  a.tw[0] = c.twT();
+  a.tw[1] = c.tw64();
+  a.nbs = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (std::max(p.B, nzero) + 255) / 256));
+  a.nbs = (int)std::max<int64_t>(a.nbs, (p.B + 255) / 256);
+  a.nbt = (int)((p.twT + 255) / 256);
+  int nu = 0;
+  if (ulp) {
+    a.ulp = *ulp;
+    a.part = (double*)(c.ws + p.off_ulp);
+    nu = ulp_slots(ulp->n);
+  }
+  hipLaunchKernelGGL(setup_kernel, dim3((unsigned)(a.nbs + 2 * a.nbt + nu)), dim3(256), 0, c.s, a);
   return hipGetLastError();
 }
 
@@ -1598,10 +1648,7 @@ int32_t pretune_group(const Plan& p0, char* ws, hipStream_t s) {
   StateInit one;
   memset(&one, 0, sizeof(one));
   one.max_iter = 1;
-  hipLaunchKernelGGL(state_init_kernel, dim3((unsigned)std::max<int64_t>(1, (p.B + 255) / 256)), dim3(256), 0, s,
-                     c.st(), p.B, (const StateInit*)nullptr, one, (unsigned long long*)nullptr, (int64_t)0);
-  HIPCHK(hipGetLastError());
-  HIPCHK(write_twiddles(c));
+  HIPCHK(run_setup(c, nullptr, one, nullptr, 0));
   return tune_plan<T>(p, ws, s, false);
 }
 
@@ -1798,10 +1845,10 @@ struct GroupRun {
       HIPCHK(hipMemcpyAsync((void*)arr, h, sizeof(StateInit) * p.B, hipMemcpyHostToDevice, s));
     }
     const int64_t nviol = user_viol ? (int64_t)max_iter + 1 : vstride * p.B;
-    const int64_t nthr = std::max<int64_t>(p.B, nviol);
-    hipLaunchKernelGGL(state_init_kernel, dim3((unsigned)std::max<int64_t>(1, (nthr + 255) / 256)), dim3(256), 0, s,
-                       c.st(), p.B, arr, one, viol, nviol);
-    HIPCHK(hipGetLastError());
+    // an FP32 field whose margin is not given: its ulp partials with the set-up
+    const MarginJob mjob{(const float*)inst[0].x_orig, p.N, inst[0].delta_f, 0};
+    const bool from_x = p.B == 1 && p.dt == FFCZ_F32 && (bc ? !(mus && mus[0] > 0.0) : ed ? ed->derive : !mus);
+    HIPCHK(run_setup(c, arr, one, viol, nviol, from_x ? &mjob : nullptr));
     if (bc) {
       // the bound pairs into the spectrum layout, their checks and minimum, then mu and the factors
       if (p.B != 1) return fail(FFCZ_E_INVALID, "pointwise bounds take one instance");
@@ -1821,12 +1868,6 @@ struct GroupRun {
       }
       double* slots = (double*)(ws + p.off_ulp);
       const double mu_given = mus ? mus[0] : 0.0;
-      if (p.dt == FFCZ_F32 && !(mu_given > 0.0)) {
-        const MarginJob one_job{(const float*)inst[0].x_orig, p.N, 0.0, 0};
-        hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)ulp_slots(p.N)), dim3(256), 0, s, one_job,
-                           (const MarginJob*)nullptr, slots);
-        HIPCHK(hipGetLastError());
-      }
       hipLaunchKernelGGL(bounds_margin_kernel, dim3(1), dim3(256), 0, s, (const double*)slots,
                          (const unsigned long long*)bc->minpart, nmin, p.N, (int)p.dt, bc->disk, mu_given, c.st());
       HIPCHK(hipGetLastError());
@@ -1841,10 +1882,6 @@ struct GroupRun {
       const int nsl = ulp_slots(p.N);
       double* slots = (double*)(ws + p.off_ulp);
       if (p.dt == FFCZ_F32) {
-        const MarginJob one_job{(const float*)inst[0].x_orig, p.N, inst[0].delta_f, 0};
-        hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)nsl), dim3(256), 0, s, one_job, (const MarginJob*)nullptr,
-                           slots);
-        HIPCHK(hipGetLastError());
         hipLaunchKernelGGL(absmax_part_kernel<float>, dim3((unsigned)nsl), dim3(256), 0, s,
                            (const float*)inst[0].x_orig, p.N, ed->amax);
       } else {
@@ -1857,17 +1894,10 @@ struct GroupRun {
       HIPCHK(hipGetLastError());
     } else if (!mus) {
       if (p.B != 1 || p.dt != FFCZ_F32) return fail(FFCZ_E_INVALID, "device margin needs one FP32 instance");
-      const int nsl = ulp_slots(p.N);
-      double* slots = (double*)(ws + p.off_ulp);
-      const MarginJob one_job{(const float*)inst[0].x_orig, p.N, inst[0].delta_f, 0};
-      hipLaunchKernelGGL(ulp_part_kernel, dim3((unsigned)nsl), dim3(256), 0, s, one_job, (const MarginJob*)nullptr,
-                         slots);
-      HIPCHK(hipGetLastError());
-      hipLaunchKernelGGL(margin_kernel, dim3(1), dim3(256), 0, s, (const double*)slots, one_job,
+      hipLaunchKernelGGL(margin_kernel, dim3(1), dim3(256), 0, s, (const double*)(ws + p.off_ulp), mjob,
                          (const MarginJob*)nullptr, (int)p.dt, (double*)nullptr, c.st());
       HIPCHK(hipGetLastError());
     }
-    HIPCHK(write_twiddles(c));
     if (bc) {
       set_variants(p, 0, 0, 0);  // the pointwise passes exist for the default tiles only
     } else if (ed) {
@@ -2008,10 +2038,7 @@ int32_t backward_impl(const Plan& p, int32_t rounds, const void* masks, const vo
   si.max_iter = rounds;
   si.pxb = gy;
   si.py = gb;
-  hipLaunchKernelGGL(state_init_kernel, dim3(1), dim3(64), 0, s, c.st(), (int64_t)1, (const StateInit*)nullptr, si,
-                     c.viol(), (int64_t)1);
-  HIPCHK(hipGetLastError());
-  HIPCHK(write_twiddles(c));
+  HIPCHK(run_setup(c, nullptr, si, nullptr, 0));
   const char* mb = (const char*)masks;
   auto splane = [&](int k) { return (uint32_t*)(mb + (size_t)k * p.s_plane_bytes); };
   auto fplane = [&](int k) {
@@ -3271,13 +3298,8 @@ int32_t decode_impl(const Plan& p, const EditLayout& L, char* ws, const void* xb
   si.px = y;  // the expanded spatial edits, read back by the closing pass
   si.pxb = xb;
   si.py = y;
-  hipLaunchKernelGGL(state_init_kernel, dim3(1), dim3(64), 0, s, c.st(), (int64_t)1, (const StateInit*)nullptr, si,
-                     c.viol(), (int64_t)1);
-  HIPCHK(hipGetLastError());
-  HIPCHK(write_twiddles(c));
   unsigned long long* tot = (unsigned long long*)(ws + L.off_tot);
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, tot, (int64_t)4);
-  HIPCHK(hipGetLastError());
+  HIPCHK(run_setup(c, nullptr, si, tot, 4));
   unsigned* status = (unsigned*)(tot + 2);
   // spatial edits straight into y (the field's dtype), frequency edits into Z
   HIPCHK(expand_set<T>(spatial_set<T>(y, L.ncs), L.nbs, (unsigned long long*)(ws + L.off_offs), tot,
@@ -3316,14 +3338,8 @@ int32_t power_bounds_impl(const Plan& p, const BoundsLayout& L, char* ws, const 
   si.inv_n = 1.0 / (double)p.N;
   si.px = ws + L.off_zero;
   si.py = const_cast<void*>(x);
-  hipLaunchKernelGGL(state_init_kernel, dim3(1), dim3(64), 0, s, c.st(), (int64_t)1, (const StateInit*)nullptr, si,
-                     c.viol(), (int64_t)1);
-  HIPCHK(hipGetLastError());
   const int64_t nz = (int64_t)p.N * (p.dt == FFCZ_F32 ? 4 : 8) / 8;
-  hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s,
-                     (unsigned long long*)(ws + L.off_zero), nz);
-  HIPCHK(hipGetLastError());
-  HIPCHK(write_twiddles(c));
+  HIPCHK(run_setup(c, nullptr, si, (unsigned long long*)(ws + L.off_zero), nz));
   const char* tb = (const char*)c.tw64();
   void* W = c.W();
   const hipError_t ez = run_row<double, T>(1, p.dt, ROW_VERIFY, kVerifyRowPlan, p, p.pitch64, p.plane64, nullptr, W,
