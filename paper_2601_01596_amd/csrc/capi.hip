@@ -3352,18 +3352,18 @@ int32_t power_bounds_impl(const Plan& p, const BoundsLayout& L, char* ws, const 
     HIPCHK(run_col<double>(1, COL_FWD_NS, 0, geom_x(p, p.pitch64, p.plane64), p, W, W, tb + 16 * p.twx, c.st(),
                            nullptr, nullptr, s));
   const SpecGeom g64{p.nrows, (int32_t)p.ncols, p.lg_rpp, p.pitch64, p.plane64};
-  const int64_t n0 = p.nd >= 2 ? p.n[0] : 1, n1 = p.nd == 3 ? p.n[1] : 1, nl = p.n[p.nd - 1];
+  const int n0 = p.nd >= 2 ? (int)p.n[0] : 1, lg1 = p.nd == 3 ? ilog2c((int)p.n[1]) : 0, nl = (int)p.n[p.nd - 1];
   double* part = (double*)(ws + L.off_shell);
   double* bins = (double*)(ws + L.off_bins);
-  hipLaunchKernelGGL(shell_part_kernel, dim3((unsigned)L.nsb), dim3(256), 0, s, (const cx<double>*)W, g64, p.nd, n0,
-                     n1, nl, L.nb, part);
+  hipLaunchKernelGGL(shell_part_kernel, dim3((unsigned)L.nsb), dim3(kShellLanes), 0, s, (const cx<double>*)W, g64, p.nd,
+                     n0, lg1, nl, L.nb, part);
   HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(shell_bound_kernel, dim3((unsigned)((L.nb + 255) / 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(shell_bound_kernel, dim3((unsigned)((L.nb + 15) / 16)), dim3(1024), 0, s,
                      (const double*)part, L.nsb, L.nb, rho, disk, bins);
   HIPCHK(hipGetLastError());
   const int64_t M = p.nrows * p.ncols;
   hipLaunchKernelGGL(shell_scatter_kernel<T>, dim3((unsigned)std::min<int64_t>(4096, (M + 255) / 256)), dim3(256), 0,
-                     s, (const double*)bins, p.nrows, (int32_t)p.ncols, p.nd, n0, n1, (T*)out);
+                     s, (const double*)bins, p.nrows, (int32_t)p.ncols, p.nd, n0, lg1, (T*)out);
   HIPCHK(hipGetLastError());
   return FFCZ_OK;
 }
