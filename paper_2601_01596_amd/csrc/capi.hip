@@ -1712,10 +1712,10 @@ struct BoundsCfg {
 };
 
 // Workspace of ffcz_correct_bounds and ffcz_power_spectrum_bounds beyond the plan's: the bound
-// pairs, block minima and a counter; for the power-spectrum bound a zero field (the verification
-// pass transforms y - x, here x - 0), the per-block shell sums and the shell bounds.
+// pairs, block minima and a counter; for the power-spectrum bound the per-block shell sums and the
+// shell bounds.
 struct BoundsLayout {
-  size_t off_D = 0, off_min = 0, off_bad = 0, off_zero = 0, off_shell = 0, off_bins = 0, bytes = 0;
+  size_t off_D = 0, off_min = 0, off_bad = 0, off_shell = 0, off_bins = 0, bytes = 0;
   int nb = 0;   // shells
   int nsb = 0;  // shell-sum blocks
 };
@@ -1736,8 +1736,6 @@ BoundsLayout bounds_layout(const Plan& p) {
   off = align_up(off + 8 * (size_t)kMinSlots, 256);
   L.off_bad = off;
   off = align_up(off + 8, 256);
-  L.off_zero = off;
-  off = align_up(off + ts * (size_t)p.N, 256);
   L.off_shell = off;
   off = align_up(off + 8 * 3 * (size_t)L.nsb * (size_t)L.nb, 256);
   L.off_bins = off;
@@ -3328,7 +3326,7 @@ int32_t decode_impl(const Plan& p, const EditLayout& L, char* ws, const void* xb
 
 // Pointwise spectral bound that keeps every shell of the power spectrum of x within rho:
 // FP64 spectrum of x on the verification passes (their last-axis pass forms y - x; here y = x
-// and x = a zero field), shell sums, shell bounds, then the bound of every entry.
+// and no x is given, read as zero), shell sums, shell bounds, then the bound of every entry.
 template <typename T>
 int32_t power_bounds_impl(const Plan& p, const BoundsLayout& L, char* ws, const void* x, double rho, int disk,
                           void* out, hipStream_t s) {
@@ -3336,10 +3334,8 @@ int32_t power_bounds_impl(const Plan& p, const BoundsLayout& L, char* ws, const 
   StateInit si;
   memset(&si, 0, sizeof(si));
   si.inv_n = 1.0 / (double)p.N;
-  si.px = ws + L.off_zero;
   si.py = const_cast<void*>(x);
-  const int64_t nz = (int64_t)p.N * (p.dt == FFCZ_F32 ? 4 : 8) / 8;
-  HIPCHK(run_setup(c, nullptr, si, (unsigned long long*)(ws + L.off_zero), nz));
+  HIPCHK(run_setup(c, nullptr, si, nullptr, 0));
   const char* tb = (const char*)c.tw64();
   void* W = c.W();
   const hipError_t ez = run_row<double, T>(1, p.dt, ROW_VERIFY, kVerifyRowPlan, p, p.pitch64, p.plane64, nullptr, W,

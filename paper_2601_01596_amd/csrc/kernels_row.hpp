@@ -280,7 +280,9 @@ row_kernel(RowArgs<T, TIO> a) {
           const int64_t gi = (lrow0 + r) * HQ + q;
           xa[u] = make_float4(0.f, 0.f, 0.f, 0.f);
           xbv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if constexpr (MODE != ROW_BINIT) {
+          if constexpr (MODE == ROW_VERIFY) {
+            if (ok && x4) xa[u] = x4[gi];  // x null: the spectrum of y itself
+          } else if constexpr (MODE != ROW_BINIT) {
             if (ok) xa[u] = x4[gi];
           }
           if (ok) xbv[u] = b4[gi];
@@ -321,7 +323,10 @@ row_kernel(RowArgs<T, TIO> a) {
           const int r = f / H, m = f - r * H;
           const bool ok = b0 + u < NL && f < ROWS * H && r < nrow;
           const int64_t gi = (lrow0 + r) * H + m;
-          if constexpr (MODE != ROW_BINIT) {
+          if constexpr (MODE == ROW_VERIFY) {
+            xa[u].x = xa[u].y = TIO(0);
+            if (ok && x2) xa[u] = x2[gi];  // x null: the spectrum of y itself
+          } else if constexpr (MODE != ROW_BINIT) {
             if (ok) xa[u] = x2[gi];
           }
           if (ok) xbv[u] = b2[gi];
