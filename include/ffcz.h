@@ -189,7 +189,7 @@ int32_t ffcz_correct(int32_t dtype, int32_t ndim, const int64_t* shape, const vo
  * same correction, with the workspace taken from a fixed device array of
  * FFCZ_NOALLOC_SCRATCH_BYTES bytes that the library holds, one copy per GPU,
  * from the first call on that GPU until the process ends.  The call allocates
- * nothing (no hipMalloc, no pinned staging, no graph instantiation): the
+ * nothing (no hipMalloc, no pinned staging): the
  * rounds run as plain launches and the tile plans come from the tuning table
  * or the defaults (nothing is timed).
  *   Arguments and results as ffcz_correct, without workspace / workspace_bytes.
@@ -482,6 +482,10 @@ void ffcz_profile_select(uint32_t kinds);
  * also have a radix-8 stage plan (the default is radix 16) and, for FP32 rows of
  * 256 entries, a direct form (rows moved straight between HBM and registers),
  * both of which round differently.
+ * In mode 1, 3D fields with small planes (one x index), without masks, edits or
+ * pointwise bounds, run a round's y-inverse, last-axis and y-forward passes as one
+ * pass over planes held in LDS, with the transforms of the default plans (profiled
+ * as the last-axis pass); the other modes keep the separate passes.
  *   mode 0  always the default plans;
  *   mode 1  (default) on the first use of a pass geometry on a device
  *           architecture, time every variant once on the call's own workspace
