@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(256) bounds_setup_kernel(const T* dre, const T
   auto check = [&](T br, T bi) {
     const bool ok = isfinite(br) && isfinite(bi) && br >= T(0) && bi >= T(0);
     nbad += ok ? 0 : 1;
-    const T m = br < bi ? br : bi;
+    const T m = (br < bi ? br : bi) + T(0);  // -0 to 0: its bits would order above every bound
     if (ok) mn = mn < m ? mn : m;
   };
   struct alignas(2 * sizeof(cx<T>) < 16 ? 16 : 2 * sizeof(cx<T>)) Pair {
