@@ -41,6 +41,7 @@
 #include "kernels_plane.hpp"
 #include "kernels_sig.hpp"
 #include "launch.hpp"
+#include "posts.hpp"
 #include "sig_dispatch.hpp"
 
 namespace ffcz {
@@ -1318,26 +1319,21 @@ struct Streams {
 };
 thread_local Streams g_streams;
 
-// The words the control kernels post checks to (Post): pinned host memory of the calling
-// thread, a new tag for every call, so that a word of an earlier call is never taken for this
-// one's.
-struct Posts {
-  unsigned long long* p = nullptr;
-  size_t n = 0;
-  unsigned long long tag = 0;
+// The words the control kernels post checks to: pinned host memory of the calling thread.
+struct Posts : PostWords {
   ~Posts() {
     if (p) (void)hipHostFree(p);
   }
   hipError_t start(size_t words) {
-    tag = tag == 0xffffff ? 1 : tag + 1;
-    if (words <= n) return hipSuccess;
-    if (p) (void)hipHostFree(p);
-    p = nullptr;
-    n = 0;
-    const hipError_t e = hipHostMalloc((void**)&p, words * sizeof(*p), hipHostMallocMapped | hipHostMallocCoherent);
-    if (e != hipSuccess) return e;
-    n = words;
-    memset(p, 0, words * sizeof(*p));
+    if (words > n) {
+      if (p) (void)hipHostFree(p);
+      p = nullptr;
+      n = 0;
+      const hipError_t e = hipHostMalloc((void**)&p, words * sizeof(*p), hipHostMallocMapped | hipHostMallocCoherent);
+      if (e != hipSuccess) return e;
+      n = words;
+    }
+    begin(words);
     return hipSuccess;
   }
   Post at(size_t i) const { return Post{p + i, tag}; }
@@ -1368,9 +1364,8 @@ int32_t drive(std::vector<RoundTask>& tasks, int32_t max_iter) {
       if (t.done) continue;
       int low = INT_MAX;
       for (size_t i = 0; i < t.n; ++i) {
-        const unsigned long long v = __atomic_load_n(g_posts.p + t.w0 + i, __ATOMIC_RELAXED);
-        if ((v >> 40) != g_posts.tag) low = 0;
-        else if (!((v >> 32) & 1)) low = std::min(low, (int)(v & 0xffffffffu));
+        const PostWords::Seen v = g_posts.read(t.w0 + i);
+        if (!v.done) low = std::min(low, v.checks);
       }
       if (low == INT_MAX) {
         t.done = true;
@@ -1406,9 +1401,8 @@ int32_t drive(std::vector<RoundTask>& tasks, int32_t max_iter) {
           if (t.done) continue;
           bool fresh = true;  // every instance posted the check of the last enqueued round, or is done
           for (size_t i = 0; i < t.n; ++i) {
-            const unsigned long long v = __atomic_load_n(g_posts.p + t.w0 + i, __ATOMIC_RELAXED);
-            const bool mine = (v >> 40) == g_posts.tag;
-            fresh = fresh && mine && (((v >> 32) & 1) || (int)(v & 0xffffffffu) >= t.enq);
+            const PostWords::Seen v = g_posts.read(t.w0 + i);
+            fresh = fresh && (v.done || (v.checks > 0 && v.checks >= t.enq));
           }
           if (!fresh) stuck = true;
         }
