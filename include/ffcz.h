@@ -97,7 +97,9 @@ typedef struct {
    * decision (ffcz_set_tuning): on its first use on a device architecture (per
    * data type and power-of-two bucket of the class's signal count) both forms
    * run three fixed rounds on the call's own members, before the correction,
-   * and the faster is kept; with tuning off, classes from 2^14 run tiled.
+   * and the faster is kept (a saved decision holds for the two forms that it
+   * compared: an entry of other forms is timed again); with tuning off, classes
+   * from 2^14 run tiled.
    * Both forms give bit-identical results. */
   int32_t tiled_1d_lg;
   /* 1 (default): a 1D member that runs on one block keeps its work buffer in

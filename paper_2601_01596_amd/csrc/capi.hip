@@ -2585,20 +2585,26 @@ int32_t sig_tables(const BatchPlan& bp, char* ws, hipStream_t s) {
 // otherwise classes below 2^kSigTiledMinLg run one block per signal, classes above 2^16 run
 // tiled, and the ones between take the tuner's decision for (architecture, data type, work
 // length, power-of-two bucket of the class's signal count, kinds of length): variant 0 is the
-// default rule (tiled from 2^14), variant 1 the other form.
+// default rule (tiled from 2^14), variant 1 the other form.  The key also names what was compared:
+// the form of variant 0, whether the one-block loop is resident, and the revision of the two forms'
+// kernels, to be raised with any change of either; an entry of another comparison is not found,
+// and the class is timed again.
 constexpr int kSigTuneMaxLg = 16;
-std::string sig_tune_key(const BatchPlan& bp, int lg) {
+constexpr int kSigFormRev = 2;
+bool sig_default_tiled(int lg) { return lg >= 14; }
+bool sig_resident(const ffcz_options& o, int dt, int lg) { return o.resident_1d != 0 && sig_res_fits(dt, lg); }
+std::string sig_tune_key(const BatchPlan& bp, const ffcz_options& o, int lg) {
   const std::vector<int>& ids = bp.by_mc.at(lg);
   int n = 1;
   while (n < (int)ids.size()) n <<= 1;
   bool blue = false, p2 = false;
   for (int k : ids) (bp.sigs[k].blue ? blue : p2) = true;
-  char buf[160];
-  snprintf(buf, sizeof(buf), "%s %s sig lg=%d n<=%d kinds=%s%s", device_arch().c_str(),
-           bp.dt == FFCZ_F32 ? "f32" : "f64", lg, n, blue ? "b" : "", p2 ? "p" : "");
+  char buf[192];
+  snprintf(buf, sizeof(buf), "%s %s sig lg=%d n<=%d kinds=%s%s 0=%s res=%d rev=%d", device_arch().c_str(),
+           bp.dt == FFCZ_F32 ? "f32" : "f64", lg, n, blue ? "b" : "", p2 ? "p" : "",
+           sig_default_tiled(lg) ? "tiled" : "block", sig_resident(o, bp.dt, lg) ? 1 : 0, kSigFormRev);
   return buf;
 }
-bool sig_default_tiled(int lg) { return lg >= 14; }
 
 // The decision for class lg without timing (the table's entry, else the default rule).
 int32_t sig_class_tiled(const BatchPlan& bp, const ffcz_options& o, int lg, hipStream_t s, bool* tiled) {
@@ -2611,7 +2617,7 @@ int32_t sig_class_tiled(const BatchPlan& bp, const ffcz_options& o, int lg, hipS
     return FFCZ_OK;
   }
   int v = 0;
-  int32_t r = tune_pass(sig_tune_key(bp, lg), s, false, 0.9f, 2, [](int) { return hipSuccess; }, &v);
+  int32_t r = tune_pass(sig_tune_key(bp, o, lg), s, false, 0.9f, 2, [](int) { return hipSuccess; }, &v);
   if (r != FFCZ_OK) return r;
   *tiled = sig_default_tiled(lg) != (v == 1);
   return FFCZ_OK;
@@ -2637,7 +2643,7 @@ hipError_t sig_trial(const BatchPlan& bp, char* ws, const int32_t* ord, int lg, 
   if (blue)
     for (int m : {(int)SIGT_CHIRP, (int)SIGT_BCOL, (int)SIGT_BROW})
       if ((e = go(m)) != hipSuccess) return e;
-  if (!tiled) return go(resident && sig_res_fits(bp.dt, lg) ? SIG_RUNL : SIG_RUN);
+  if (!tiled) return go(resident ? SIG_RUNL : SIG_RUN);
   if ((e = go(SIGT_EPS0)) != hipSuccess) return e;
   if ((e = go(SIGT_CIN)) != hipSuccess) return e;
   int nct = 0, nrt = 0;
@@ -2673,11 +2679,11 @@ int32_t pretune_sigs(const BatchPlan& bp, const ffcz_options& o, char* ws, hipSt
     const int32_t* ord = (const int32_t*)(ws + bp.off_order) + first.at(lg);
     const bool dflt = sig_default_tiled(lg);
     int v = 0;
-    int32_t r = tune_pass(sig_tune_key(bp, lg), s, true, 0.9f, 2, [&](int var) {
+    int32_t r = tune_pass(sig_tune_key(bp, o, lg), s, true, 0.9f, 2, [&](int var) {
       const bool tiled = dflt != (var == 1);
       ran = true;
-      return bp.dt == FFCZ_F32 ? sig_trial<float>(bp, ws, ord, lg, tiled, o.resident_1d != 0, 3, s)
-                               : sig_trial<double>(bp, ws, ord, lg, tiled, o.resident_1d != 0, 3, s);
+      return bp.dt == FFCZ_F32 ? sig_trial<float>(bp, ws, ord, lg, tiled, sig_resident(o, bp.dt, lg), 3, s)
+                               : sig_trial<double>(bp, ws, ord, lg, tiled, sig_resident(o, bp.dt, lg), 3, s);
     }, &v);
     if (r != FFCZ_OK) return r;
   }
@@ -2839,7 +2845,7 @@ struct SigRun {
       const bool t = lg >= kSigTiledMinLg;
       if (t) HIPCHK(setup_tables(lg, sb));
       else HIPCHK(go(SIG_SETUP, lg, sb));
-      HIPCHK(go(o.resident_1d && sig_res_fits(bp->dt, lg) ? SIG_RUNL : SIG_RUN, lg, sb));
+      HIPCHK(go(sig_resident(o, bp->dt, lg) ? SIG_RUNL : SIG_RUN, lg, sb));
       if (!o.verify_fp64) continue;
       if (t) HIPCHK(verify_tiled(lg, sb));
       else HIPCHK(go(SIG_VERIFY, lg, sb));
