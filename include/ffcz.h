@@ -84,7 +84,8 @@ typedef struct {
    * the loop is polled in chunks (use_graph = 0 and ffcz_correct_noalloc). */
   int32_t graph_chunk;
   /* 1 (default): the device posts every check's outcome to pinned host memory and
-   * the host enqueues the next round while the passes after the check still run;
+   * the host enqueues the next round while the passes after the check still run (the
+   * calling thread watches the words, and yields its core while a wait is long);
    * 0: chunks of rounds with one poll per chunk.  Identical results. */
   int32_t use_graph;
   /* Batched 1D members whose power-of-two work length Mc (Mc = L for a

@@ -30,6 +30,7 @@
 #include <map>
 #include <memory>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/ffcz.h"
@@ -1357,7 +1358,8 @@ struct RoundTask {
 // one poll per chunk, measured before: 64^3 FP64, 4 rounds, 238 us, of which 3 rounds of early
 // returns 30 us, two polls 30 us; a new workspace paid for a capture.)
 int32_t drive(std::vector<RoundTask>& tasks, int32_t max_iter) {
-  auto last_query = std::chrono::steady_clock::now();
+  using std::chrono::microseconds;
+  auto last_query = std::chrono::steady_clock::now(), since = last_query;  // since: the last round enqueued
   for (;;) {
     bool all = true, moved = false;
     for (RoundTask& t : tasks) {
@@ -1379,9 +1381,17 @@ int32_t drive(std::vector<RoundTask>& tasks, int32_t max_iter) {
       }
     }
     if (all) return FFCZ_OK;
-    if (moved) continue;
     const auto now = std::chrono::steady_clock::now();
-    if (now - last_query > std::chrono::microseconds(200)) {
+    if (moved) {
+      since = now;
+      continue;
+    }
+    // rounds of small fields take tens of microseconds, which a scheduled-out thread would miss;
+    // a longer wait leaves the core to whoever else is ready (a call with 0.6 s of work ahead of it
+    // on its stream and a busy process on its core: half of the core each with spinning alone, less
+    // than 1 % of it for this thread now)
+    if (now - since > microseconds(200)) std::this_thread::yield();
+    if (now - last_query > microseconds(200)) {
       // a stream that failed, or drained without posting, ends the wait
       last_query = now;
       bool idle = true;
