@@ -1318,7 +1318,26 @@ struct Streams {
     return e;
   }
 };
-thread_local Streams g_streams;
+// The calling thread's streams beside the stream s, on its device: a launch runs on its stream's
+// device, whatever device is current, so a thread that serves several devices must not send one's
+// work down another's streams.
+hipError_t streams_of(hipStream_t s, Streams** out) {
+  thread_local std::map<int, Streams> of;
+  int dev = 0, cur = 0;
+  hipError_t e = hipGetDevice(&cur);
+  if (e != hipSuccess) return e;
+  // (the null stream is the current device's, and so is a handle that names no stream of its own)
+  if (!s || hipStreamGetDevice(s, &dev) != hipSuccess) {
+    (void)hipGetLastError();
+    dev = cur;
+  }
+  *out = &of[dev];
+  if (dev == cur) return (*out)->ready();
+  if ((e = hipSetDevice(dev)) != hipSuccess) return e;
+  e = (*out)->ready();
+  const hipError_t back = hipSetDevice(cur);
+  return e != hipSuccess ? e : back;
+}
 
 // The words the control kernels post checks to: pinned host memory of the calling thread.
 struct Posts : PostWords {
@@ -2728,6 +2747,7 @@ struct SigRun {
   char* ws = nullptr;
   hipStream_t s = nullptr;       // set-up, tiled passes, end (lane 0)
   SigLanes lanes;                // the streams of set-up and end
+  Streams* own = nullptr;        // the call's streams and events
   hipStream_t side = nullptr;    // one-block classes (joined into s at the end)
   hipEvent_t fork = nullptr, join = nullptr;
   std::map<int, int> first;      // class -> first slot in the block order
@@ -2800,21 +2820,20 @@ struct SigRun {
   hipError_t across(const SigLanes& L, F&& f) const {
     const int n = lanes_used(L);
     hipError_t e = hipSuccess;
-    if (n > 1) e = hipEventRecord(g_streams.lfork, L.q[0]);
-    for (int k = 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(L.q[k], g_streams.lfork, 0);
+    if (n > 1) e = hipEventRecord(own->lfork, L.q[0]);
+    for (int k = 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(L.q[k], own->lfork, 0);
     if (e != hipSuccess) return e;
     e = spread(L, f);
     for (int k = 1; k < n; ++k) {
-      hipError_t j = hipEventRecord(g_streams.ljoin[k - 1], L.q[k]);
-      if (j == hipSuccess) j = hipStreamWaitEvent(L.q[0], g_streams.ljoin[k - 1], 0);
+      hipError_t j = hipEventRecord(own->ljoin[k - 1], L.q[k]);
+      if (j == hipSuccess) j = hipStreamWaitEvent(L.q[0], own->ljoin[k - 1], 0);
       if (e == hipSuccess) e = j;
     }
     return e;
   }
 
   int32_t begin(const BatchPlan& bp_, int32_t max_iter_, const ffcz_options& o_, char* ws_,
-                const std::map<int, int>& first_, const SigLanes& lanes_, hipStream_t side_, hipEvent_t fork_,
-                hipEvent_t join_) {
+                const std::map<int, int>& first_, const SigLanes& lanes_, Streams& own_) {
     bp = &bp_;
     max_iter = max_iter_;
     o = o_;
@@ -2822,9 +2841,10 @@ struct SigRun {
     first = first_;
     lanes = lanes_;
     s = lanes.q[0];
-    side = side_;
-    fork = fork_;
-    join = join_;
+    own = &own_;
+    side = own->side2;
+    fork = own->fork2;
+    join = own->join2;
     fixed = o.fixed_iterations ? 1 : 0;
     chunk = o.graph_chunk > 0 ? o.graph_chunk : 4;
     if (nsig() == 0) return FFCZ_OK;
@@ -2956,8 +2976,8 @@ struct SigRun {
   // outlives the call)
   int32_t rejoin() {
     for (int k = 1; k < lanes.n && lanes.q[k]; ++k) {
-      HIPCHK(hipEventRecord(g_streams.ljoin[k - 1], lanes.q[k]));
-      HIPCHK(hipStreamWaitEvent(s, g_streams.ljoin[k - 1], 0));
+      HIPCHK(hipEventRecord(own->ljoin[k - 1], lanes.q[k]));
+      HIPCHK(hipStreamWaitEvent(s, own->ljoin[k - 1], 0));
     }
     lanes.n = 1;
     if (!side_used) return FFCZ_OK;
@@ -2972,10 +2992,10 @@ struct SigRun {
 int32_t run_sigs(const BatchPlan& bp, int32_t max_iter, const ffcz_options& o, char* ws, hipStream_t s,
                  const std::map<int, int>& first, HostBuf& hstate) {
   if (bp.sig_ids.empty()) return FFCZ_OK;
-  HIPCHK(g_streams.ready());
+  Streams* q = nullptr;
+  HIPCHK(streams_of(s, &q));
   SigRun sr;
-  int32_t r = sr.begin(bp, max_iter, o, ws, first, SigLanes{3, {s, g_streams.lane1, g_streams.side}},
-                       g_streams.side2, g_streams.fork2, g_streams.join2);
+  int32_t r = sr.begin(bp, max_iter, o, ws, first, SigLanes{3, {s, q->lane1, q->side}}, *q);
   if (r != FFCZ_OK) return r;
   r = sr.loop(hstate);
   if (r != FFCZ_OK) return r;
@@ -3058,10 +3078,11 @@ __global__ void __launch_bounds__(256) copy_columns_kernel(char* __restrict__ ds
 // 1D launch still writes the caller's buffers once the call has returned.
 struct SideJoin {
   hipStream_t s = nullptr, s1 = nullptr;
+  hipEvent_t join = nullptr;
   ~SideJoin() {
     if (s1 && s1 != s) {
-      (void)hipEventRecord(g_streams.join, s1);
-      (void)hipStreamWaitEvent(s, g_streams.join, 0);
+      (void)hipEventRecord(join, s1);
+      (void)hipStreamWaitEvent(s, join, 0);
     }
   }
 };
@@ -3083,16 +3104,17 @@ int32_t mixed_batch(const BatchPlan& bp, const ffcz_instance* inst, const std::v
   }
   int32_t r = pretune_sigs(bp, o, w, s, first);
   if (r != FFCZ_OK) return r;
-  HIPCHK(g_streams.ready());
-  const hipStream_t s1 = g_streams.side;
-  HIPCHK(hipEventRecord(g_streams.fork, s));
-  HIPCHK(hipStreamWaitEvent(s1, g_streams.fork, 0));
+  Streams* q = nullptr;
+  HIPCHK(streams_of(s, &q));
+  const hipStream_t s1 = q->side;
+  HIPCHK(hipEventRecord(q->fork, s));
+  HIPCHK(hipStreamWaitEvent(s1, q->fork, 0));
   SideJoin side;  // s waits for s1 on every exit from here
   side.s = s;
   side.s1 = s1;
+  side.join = q->join;
   SigRun sr;      // declared after the join: its own stream joins s1 first
-  r = sr.begin(bp, max_iter, o, w, first, SigLanes{2, {s1, g_streams.lane1, nullptr}}, g_streams.side2,
-               g_streams.fork2, g_streams.join2);
+  r = sr.begin(bp, max_iter, o, w, first, SigLanes{2, {s1, q->lane1, nullptr}}, *q);
   if (r != FFCZ_OK) return r;
   // the groups' set-up on s; their instance and margin arrays live as long as the runs
   const size_t ng = bp.groups.size();
