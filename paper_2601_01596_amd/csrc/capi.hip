@@ -1670,18 +1670,28 @@ int32_t tune_plan(Plan& p, char* ws, hipStream_t s, bool rec, bool no_time = fal
 }
 
 // Whether a field's rounds run on the plane pass: one block does a whole plane, so a plane must
-// either be small (a few us a block) or come in numbers that keep the chip busy.  20 rounds,
-// separate passes -> plane pass, us (MI355X): planes of 17-35 KB 64 x 64 x 64 FP64 624 -> 421,
-// 4 x 64 x 64 FP32 478 -> 329, 64 x 64 x 128 FP32 642 -> 466; of 66 KB 128^3 FP32 1014 -> 796, 64 x 256 x 64
-// 760 -> 700, but 8 x 256 x 64 551 -> 590; of 131 KB 512 x 64 x 128 1224 -> 1022, 256 x 512 x 64 FP32 1806 -> 1626,
-// 128^3 FP64 1198 -> 1074, but 128 x 512 x 64 FP32 1184 -> 1199, 64 x 256 x 128 FP32 1031 -> 1076 and
-// 32 x 128 x 256 FP32 794 -> 952.
+// either be small (a few us a block) or come in numbers that keep the chip busy.  And with enough
+// planes to fill the chip several times over, what counts is each pass's rate, not its launch and
+// its latency: with rows of 64 entries and more the separate passes' is the higher one (longer y
+// transforms make up for it in FP64 planes of 128 KB).  20 rounds, separate -> plane pass, us
+// (MI355X; n0 x n1 x n2):
+//   up to 32 KB  64 x 64 x 64 FP64 616 -> 414, 2 x 64 x 64 FP32 497 -> 306, 64 x 64 x 128 FP32 604 -> 460;
+//                512 x 64 x 128 FP32 1119 -> 1031, but 1024: 1755 -> 1806 and 2048: 3107 -> 3433;
+//                1024 x 32 x 128 FP64 1713 -> 1846; 2048 x 32 x 256 FP32 2890 -> 3358
+//   64 KB        64 x 256 x 64 FP32 757 -> 699, but 16: 590 -> 626; 64 x 64 x 128 FP64 723 -> 643;
+//                512 x 128 x 128 FP32 1621 -> 1480, but 2048: 6151 -> 6382; 1024 x 32 x 256 FP64 2822 -> 2924
+//   128 KB FP32  256 x 512 x 64 1790 -> 1611, but 128: 1182 -> 1192; 256 x 128 x 256 1458 -> 1363,
+//                but 512: 2448 -> 2488 and 1024: 5061 -> 5195; 512 x 256 x 128 2701 -> 2620
+//   128 KB FP64  128 x 128 x 128 1137 -> 1074, but 64: 958 -> 965; 1024 x 64 x 256 5021 -> 4711
 bool plane_rule(const Plan& p) {
   const int64_t planes = p.n[0] * p.B;
+  const bool f32 = p.dt == FFCZ_F32;
   if (p.nd != 3 || planes > p.pmax) return false;
-  if (!(p.dt == FFCZ_F32 ? plane_fits<float>(p.Ly, p.H) : plane_fits<double>(p.Ly, p.H))) return false;
-  const int64_t kb = (int64_t)p.Ly * p.H * (p.dt == FFCZ_F32 ? 8 : 16) / 1024;
-  if (kb > 32 && planes < (kb <= 64 ? 64 : p.dt == FFCZ_F32 ? 256 : 128)) return false;
+  if (!(f32 ? plane_fits<float>(p.Ly, p.H) : plane_fits<double>(p.Ly, p.H))) return false;
+  const int64_t kb = (int64_t)p.Ly * p.H * (f32 ? 8 : 16) / 1024;
+  if (kb > 32 && planes < (kb <= 64 ? 64 : f32 ? 256 : 128)) return false;
+  if (p.Ly > 16 && p.H >= 64 && planes >= 1024 && (f32 || kb <= 64)) return false;
+  if (f32 && kb > 64 && p.H >= 128 && planes >= 512) return false;
   std::lock_guard<std::mutex> g(g_tuner.m);
   g_tuner.init_locked();
   return g_tuner.mode == 1;  // the other modes ask for the separate passes' plans

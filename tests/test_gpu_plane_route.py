@@ -46,3 +46,19 @@ def test_other_fields_take_separate_passes(dt, shape, kw):
     (_, res), n = _launches(lambda: run_gpu(p.x, p.xb, p.E, p.Delta, 3, fixed=True, **kw))
     assert res.stats["rounds"] == 3
     assert n["y_inv"] == 3 and n["y_fwd"] == 4, n
+
+
+# many planes of rows of 64 entries and more: the separate passes are the faster ones from 1024 planes
+# on (512 where an FP32 plane has more than 64 KB and rows of 128)
+@pytest.mark.parametrize("dt,shape,one", [(np.float32, (1024, 32, 128), False), (np.float32, (512, 32, 128), True),
+                                          (np.float64, (1024, 32, 128), False), (np.float32, (1024, 64, 64), True),
+                                          (np.float32, (512, 128, 256), False), (np.float32, (512, 64, 256), True)])
+def test_many_planes_of_long_rows_take_separate_passes(dt, shape, one):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.randn(shape, generator=g, device="cuda").to(torch.float32 if dt == np.float32 else torch.float64)
+    xb = x + 0.01 * (torch.rand(shape, generator=g, device="cuda").to(x.dtype) - 0.5)
+    r, n = _launches(lambda: F.correct(x, xb, 0.005, 0.05 * x.numel() ** 0.5, 2, fixed=True, check=False))
+    assert r.stats["rounds"] == 2
+    assert n["y_inv"] == (0 if one else 2), n
