@@ -1378,6 +1378,14 @@ struct RoundTask {
 // returns 30 us, two polls 30 us; a new workspace paid for a capture.)
 int32_t drive(std::vector<RoundTask>& tasks, int32_t max_iter) {
   using std::chrono::microseconds;
+  // captured work never runs, so nothing would be posted: refused like any wait under capture
+  for (const RoundTask& t : tasks) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing(t.s, &cs));
+    if (cs == hipStreamCaptureStatusNone) continue;
+    HIPCHK(hipStreamSynchronize(t.s));  // an error here, which also ends the capture
+    return fail(FFCZ_E_HIP, "the rounds wait for the device: not while the stream is being captured");
+  }
   auto last_query = std::chrono::steady_clock::now(), since = last_query;  // since: the last round enqueued
   for (;;) {
     bool all = true, moved = false;
