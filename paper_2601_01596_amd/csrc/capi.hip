@@ -10,8 +10,11 @@
 // (2D: x-pass Z -> A, ctl, z-pass A -> Z; 1D fields: the x-pass has length 1.)
 // Z therefore always holds the last-axis R2C of the iterate whose check is
 // running, so when that check passes the output is the C2R of Z.  Every loop
-// kernel returns at entry once its instance's done-flag is set, so the host
-// enqueues rounds in chunks and polls the flags once per chunk.
+// kernel returns at entry once its instance's done-flag is set, and the control
+// kernel posts each check to pinned host memory: the host enqueues a round once
+// the check before it is in (drive), or, where asked to, chunks of rounds with
+// one poll of the flags each.  Small 3D fields run y-inv, z-pass and the next
+// round's y-fwd as one pass over planes, which also makes the check.
 //
 // A plan covers B instances of one shape (B = 1 for ffcz_correct): their
 // spectra are stacked, so one launch of each pass serves all of them, while
@@ -314,7 +317,8 @@ bool has_direct(const Plan& p) { return p.dt == FFCZ_F32 && (p.H == 128 || p.H =
 int init_variant(const Plan& p) { return p.vz >= 3 && has_direct(p) ? p.vz : 0; }
 // Last-axis plan of calls with masks (and of the adjoint) where the table holds none: nothing is
 // timed for them, and a mask bit is a decision that another rounding can turn, so the direct
-// form that keeps the default plan's bits (256^3 FP32, loop and adjoint pass: 39.9 -> 32.3 us, so a gradient of 50 rounds 12.81 -> 12.17 ms).
+// form that keeps the default plan's bits (256^3 FP32, loop pass 39.9 -> 31.8 us, adjoint pass 33.1;
+// a gradient of 50 rounds 12.81 -> 12.25 ms).
 int masked_variant(const Plan& p, int vz) { return vz == 0 && has_direct(p) ? 4 : vz; }
 
 // Neighbouring column tiles that read parts of the same 128-byte lines (1 when a tile row fills
@@ -619,8 +623,8 @@ __global__ void __launch_bounds__(256) ulp_part_kernel(MarginJob one, const Marg
 // Everything a call writes or sums before its first pass, side by side in one launch: instance
 // states (nbs blocks; they also clear nzero words), the twiddle tables of both precisions (nbt
 // blocks each) and, where the margin comes from x, the ulp partials of x (the rest).  Three
-// launches of 4-7 us in a row before: 64^3 FP64 156 -> 149 us a correction, 64 x 256 x 128 FP32
-// 230 -> 216, 2048^2 FP32 359 -> 348.
+// launches of 4-7 us in a row before: 64^3 FP64 156 -> 149 us a correction (the best of each; 150-160
+// over processes), 64 x 256 x 128 FP32 230 -> 216, 2048^2 FP32 359 -> 348.
 struct SetupArgs {
   DevState* st;
   int64_t B;
@@ -1288,9 +1292,8 @@ struct HostBuf {
   }
 };
 thread_local HostBuf g_host_state, g_host_init, g_host_misc;
-// staging of the 1D members (descriptors, then their loop states), owned by the calling
-// thread and handed to the thread that drives those members, so that no pinned buffer is
-// allocated or freed per call on a short-lived thread (hipHostFree synchronises the device)
+// staging of the 1D members (descriptors, then their loop states), apart from the grouped members',
+// which is written while copies from this one may be in flight
 thread_local HostBuf g_host_sig, g_host_sigstate;
 
 // Private streams (default priority) for the 1D members of a batch, which run beside the
@@ -1816,12 +1819,11 @@ BoundsLayout bounds_layout(const Plan& p) {
 // bounds, mus[b] the margins; mus null (one FP32 instance) derives mu from x on
 // the device, between the state set-up and the first pass.
 // host_state: when given (one entry per instance, ordinary host memory), the call
-// allocates nothing: the loop state is read back into it, the rounds run as plain
-// launches (no graph) and the tile plans come from the table or the defaults.
+// allocates nothing: the loop state is read back into it, the rounds run in polled chunks
+// and the tile plans come from the table or the defaults.
 // One group's correction (a plan over B same-shape instances) in phases: begin (set-up through
-// the first last-axis transform, on the call's stream), the rounds in chunks (run here, or
-// captured with other work by the mixed-batch loop), end (closing pass, verification,
-// statistics).  Holds a Ctx that points at its own Plan: neither copied nor moved.
+// the first last-axis transform, on the call's stream), the rounds (driven from here, or with
+// other work by the mixed-batch loop), end (closing pass, verification, statistics).  Holds a Ctx that points at its own Plan: neither copied nor moved.
 template <typename T>
 struct GroupRun {
   Plan p;
@@ -2751,8 +2753,8 @@ struct SigLanes {
 };
 
 // The 1D members of a batch in phases: begin (descriptors and tables are in place; the one-block
-// classes on their own stream, the tiled classes' set-up), the tiled rounds in chunks (run here,
-// or captured with the groups' rounds by the mixed-batch loop), end (the tiled classes' outputs
+// classes on their own stream, the tiled classes' set-up), the tiled rounds (driven from here, or with
+// the groups' rounds by the mixed-batch loop), end (the tiled classes' outputs
 // and verification, then the one-block stream joined).  Every tiled round pass returns at entry
 // once its signal's loop has ended.  A pass of one class is a small launch (10 to 40 us, mostly
 // ramp and tail, few blocks for the shorter classes) and classes do not depend on each other, so

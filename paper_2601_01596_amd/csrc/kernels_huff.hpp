@@ -2,7 +2,7 @@
 // symbols (flag bytes or int32 codes) are counted blockwise into a global frequency table,
 // the host builds the Huffman code from that table, and the stream is encoded in parallel:
 // every symbol's bit offset is an exclusive prefix sum of code lengths (block sums, one-block
-// scan, block-local scan), and each symbol ORs its code into at most two 32-bit words.
+// scan, block-local scan), and a block puts its codes together in LDS and stores whole words.
 //
 // Stream layout (bits): codes most significant bit first, each 32-bit word filled from its
 // top bit down.  The offset of every kHuffChunk-th symbol is kept, so the decoder runs one

@@ -7,8 +7,8 @@
 // through
 //     inverse along y (in place, column groups), C2R, s-clip, R2C (rows), forward along y
 // and stores it twice: the last-axis R2C (Z, the iterate a closing pass starts from) and its
-// y-forward transform (A, which the next x-pass reads).  5 M c bytes a round instead of 8 M c,
-// and three launches (x-pass, control, plane) instead of five.  Each transform runs on the stage
+// y-forward transform (A, which the next x-pass reads).  It begins with the round's check.  5 M c
+// bytes a round instead of 8 M c, and two launches (x-pass, plane) instead of five.  Each transform runs on the stage
 // plan and with the formulas of the separate passes.
 //
 // Lanes: columns fastest in the y transforms (groups of CG columns, as many as the block's lanes
